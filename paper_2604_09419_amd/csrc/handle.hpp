@@ -84,9 +84,10 @@ struct WsLayout {
     long long entries = 0, hist_n = 0, ilev_n = 0;
 };
 
+// Scratch of the alias build ([k]: 0 the negative table, 1 the edge table).
 struct ScratchLayout {
-    size_t wq = 0, dx = 0, idx = 0, lpos = 0, deg = 0, indeg = 0, cnt = 0, lev = 0, ilev = 0, total = 0;
-    long long N = 0, lev_n = 0;
+    size_t dx[2] = {}, idx[2] = {}, blk[2] = {}, tot[2] = {}, mxl[2] = {}, off[2] = {}, before[2] = {};
+    size_t total_weight = 0, deg = 0, indeg = 0, cnt = 0, total = 0;
 };
 
 WsLayout ws_layout(const lh_params &p, long long n, long long m);

@@ -63,21 +63,23 @@ WsLayout ws_layout(const lh_params &p, long long n, long long m)
 ScratchLayout scratch_layout(long long n, long long m)
 {
     ScratchLayout L;
-    long long N = n > m ? n : m;
-    if (N < 1) N = 1;
-    L.N = N;
     size_t off = 0;
-    L.wq = carve(off, 8 * (size_t)N);
-    L.dx = carve(off, 8 * (size_t)N);
-    L.idx = carve(off, 4 * (size_t)N);
-    L.lpos = carve(off, 4 * (size_t)N);
+    for (int k = 0; k < 2; ++k) {
+        const long long N = std::max(k == 0 ? n : m, 1ll), chunks = N / SCAN_CHUNK + 2;
+        L.dx[k] = carve(off, 8 * (size_t)N);
+        L.idx[k] = carve(off, 4 * (size_t)N);
+        L.blk[k] = carve(off, 4 * (size_t)chunks);
+        L.tot[k] = carve(off, 8 * (size_t)chunks);
+        L.mxl[k] = carve(off, 8 * (size_t)chunks);
+        L.off[k] = carve(off, 8 * (size_t)chunks);
+        L.before[k] = carve(off, 8 * (size_t)chunks);
+    }
+    L.total_weight = carve(off, 16);
     L.deg = carve(off, 4 * (size_t)(n > 0 ? n : 1));
     L.indeg = carve(off, 4 * (size_t)(n > 0 ? n : 1));
-    L.cnt = carve(off, 8 * 257);
-    L.lev_n = scan_levels_size(N);
-    L.lev = carve(off, 8 * (size_t)L.lev_n);
-    L.ilev = carve(off, 4 * (size_t)L.lev_n);
-    L.total = off;
+    L.cnt = carve(off, 8 * 258);
+    // (never below the 24 bytes per item that the size has always been)
+    L.total = std::max(off, lh_align_up(24 * (size_t)std::max(std::max(n, m), 1ll), 256));
     return L;
 }
 
