@@ -1,4 +1,5 @@
 // C ABI of the linehip library: argument checks, handle state, stream ordering.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -40,18 +41,20 @@ GraphDev graph_dev(const lh_handle *h)
     g.K = h->p.K;
     g.hot_heat = -1;
     g.hot_rate = h->p.hot_rate;
-    g.max_in_flight = 0.0;
-    if (h->p.max_conflicts > 0.0 && h->n_active > 0)
-        g.max_in_flight = h->p.max_conflicts * (double)h->n_active / (double)(h->p.K + 2);
-    const double b = h->p.dtype == LH_FP32 ? 4.0 : 2.0;
-    const double ntab = h->p.orders == LH_ORDER12 ? 3.0 : (h->p.orders == LH_ORDER2 ? 2.0 : 1.0);
-    const double rows = (double)(h->n_active > 0 ? h->n_active : h->n);
-    g.resid = small_table_window(h->l2_bytes, rows * h->p.d * b * ntab);
+    g.staleness = g.max_in_flight = staleness_cap(h);
+    if (h->p_max > 0.0) {
+        const double row_bytes = h->p.d * (h->p.dtype == LH_FP32 ? 4.0 : 2.0);
+        const bool more = row_bytes <= 128.0 || tables_bytes(h) > kCachedTableBytes;
+        const double F = std::max(64.0, (more ? kHottestInFlightMore : kHottestInFlight) / h->p_max);
+        if (!(g.max_in_flight > 0.0) || F < g.max_in_flight) g.max_in_flight = F;
+    }
+    g.resid = small_table_window(h->l2_bytes, tables_bytes(h));
     ShadowCtx sc;
     const bool shadowed = shadow_ctx(h, &sc);
     for (int t = 0; t < 3; ++t) g.shadow[t] = shadowed ? sc.shadow[t] : nullptr;
     g.slot = shadowed ? sc.slot : nullptr;
     g.tiles = h->ws ? (unsigned long long *)(h->ws + h->lay.tiles) : nullptr;
+    g.tile_shift = 6;
     g.pairs = nullptr;
     g.pairs_first = 0;
     g.heat = h->ws ? (const uint8_t *)(h->ws + h->lay.nheat) : nullptr;

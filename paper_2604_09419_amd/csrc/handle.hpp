@@ -27,6 +27,7 @@ struct GraphDev {
     int hot_heat;              // rows with heat <= hot_heat take atomic increments (-1: none)
     double hot_rate;           // host side: the threshold hot_heat is derived from per launch
     double max_in_flight;      // host side: cap on samples in flight (0: none)
+    double staleness;          // host side: the part of it that is the staleness cap (0: none)
     double resid;              // host side: extra hot window (infinite for tables that fit in one L2)
     // bfloat16 Hogwild: binary32 shadow rows of the hot rows ([cap x d] per table) and the
     // per-node slot map (slot >= 0: the row lives in the shadow for this launch).  NULL
@@ -34,8 +35,9 @@ struct GraphDev {
     float *shadow[3];
     const int32_t *slot;
     // Hogwild: the launch's tile counter (device word, reset to 0 before each launch);
-    // wavefronts take 64-sample tiles from it until none are left.
+    // wavefronts take tiles of 2^tile_shift samples from it until none are left.
     unsigned long long *tiles;
+    int tile_shift;
     // Positive pairs from random walks: pairs[s - pairs_first] is the (u, v) of sample s
     // (every sample of the launch lies in the buffer); NULL: slot 0 draws an arc.  heat:
     // per-node heat, for the write path of a walk pair's rows.
@@ -155,6 +157,7 @@ struct lh_handle {
     void *tab[3] = {nullptr, nullptr, nullptr};
     long long n = 0, m = 0;
     long long n_active = 0;  // nodes with at least one arc (from the last alias build)
+    double p_max = 0.0;      // touch probability of the hottest row (last build; 0 after an import)
     unsigned long long heat_count[256] = {};  // nodes per heat value (last build or import)
     const int32_t *src = nullptr, *dst = nullptr;
     const float *w = nullptr;
@@ -195,12 +198,49 @@ double hogwild_in_flight(const GraphDev &g, int dtype, int orders, const TileCfg
                          int num_cu);
 // Largest hot share at which a bfloat16 handle runs two samples per wavefront.
 constexpr double kTwoPerWaveMaxHotShare = 0.1;
+// Binary32 shapes (K = 5, second order, ns a sample on R-MAT graphs at the launch's own samples in
+// flight).  Rows of 65 to 128 units: (32, 4) up to this size of tables, which the Infinity Cache
+// still serves for the most part (300,000 nodes, 307 MB: 1.67 against 1.82), above it (64, 2),
+// whose cold rows take the streaming stores (2^20 nodes, 1.07 GB: 1.50 against 1.56).  Rows of
+// 33 to 64 units: (32, 2) (150,000 nodes: 1.76 against 1.78 for (64, 1) and 2.37 for (16, 4)).
+constexpr double kCachedTableBytes = 512.0 * 1048576.0;
+// Tables that fit in one L2 have every row updated atomically: no update is lost, and what a run
+// ends with depends on staleness alone.  There, one or two units a lane keep a sample between its
+// loads and its writes for most of a round, where four units a lane spend the round issuing
+// accesses, so at the same number of resident samples, which is what the cap counts, they are
+// several times as stale: 10,000 nodes at d = 16 train in 6.1 ns a sample but end 2-3 % (Frobenius)
+// from where four units a lane end (28 ns), whose own runs differ by 0.3-0.5 %.  Filling this
+// share of the cap, they end 0.5-1 % off in 14.3 ns.  At other widths such a share leaves no gain
+// over four units a lane (d = 32: 15.2 against 14.8 ns; d = 64: 13.0 against 8.3), which they keep.
+constexpr double kSmallTableCapShare = 0.4;
+// A launch keeps no more samples in flight than the graph's hottest row can serve: its updates are
+// atomics on the same lines, one after the other (24 ns per 256 bytes), so with p_max the
+// probability that a sample touches it, more than about latency / (p_max x that time) samples
+// only queue there, and enlarge the hot set besides.  Measured optimum over 40,000 to 2^21 nodes,
+// widths 16 to 200 and both types: p_max x samples about 32, and 48 for rows of at most 128 bytes
+// (a shorter service) and for tables beyond the Infinity Cache (a longer latency: 2^20 nodes,
+// d = 128, both orders 2.72 ns at 4,096 and 2.80 at 2,048).
+// d = 128, 150,000 nodes: 2.07 ns a sample at 1,024 in flight, 2.54 at 3,072; 300,000 nodes, both
+// orders: 3.03 at 1,536, 4.89 at 6,144.  Graphs without hubs are not limited by it.
+constexpr double kHottestInFlight = 32.0, kHottestInFlightMore = 48.0;
+// Bytes of the tables' rows that have an arc.
+inline double tables_bytes(const lh_handle *h)
+{
+    const double ntab = h->p.orders == LH_ORDER12 ? 3.0 : (h->p.orders == LH_ORDER2 ? 2.0 : 1.0);
+    return (double)(h->n_active > 0 ? h->n_active : h->n) * h->p.d * (h->p.dtype == LH_FP32 ? 4.0 : 2.0) * ntab;
+}
+// Samples in flight that lh_params.max_conflicts allows (0: no cap).
+inline double staleness_cap(const lh_handle *h)
+{
+    if (!(h->p.max_conflicts > 0.0) || h->n_active <= 0) return 0.0;
+    return h->p.max_conflicts * (double)h->n_active / (double)(h->p.K + 2);
+}
 // The Hogwild configuration of a handle none was pinned for, once its degrees are known.
 // bfloat16: two samples per wavefront (half the lanes, twice the units per lane) when at
 // most kTwoPerWaveMaxHotShare of the row touches then fall on hot rows, else one.  Two per
 // wavefront double the samples in flight, which hides more of the latency of random rows
 // in large tables, but they also enlarge the hot set, whose atomics cost more than that
-// gain where hub rows take a large share of the touches.  Binary32: default_cfg.
+// gain where hub rows take a large share of the touches.  Binary32: as above.
 TileCfg auto_cfg(const lh_handle *h);
 bool cfg_supported(int dtype, int d, const TileCfg &c);
 hipError_t launch_hogwild(const GraphDev &g, int dtype, int orders, const TileCfg &c,

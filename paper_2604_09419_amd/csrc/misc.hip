@@ -77,7 +77,7 @@ ScratchLayout scratch_layout(long long n, long long m)
     L.total_weight = carve(off, 16);
     L.deg = carve(off, 4 * (size_t)(n > 0 ? n : 1));
     L.indeg = carve(off, 4 * (size_t)(n > 0 ? n : 1));
-    L.cnt = carve(off, 8 * 258);
+    L.cnt = carve(off, 8 * 259);
     // (never below the 24 bytes per item that the size has always been)
     L.total = std::max(off, lh_align_up(24 * (size_t)std::max(std::max(n, m), 1ll), 256));
     return L;
@@ -95,7 +95,7 @@ static int next_pow2(int x)
 
 static int units_per_row(int dtype, int d) { return dtype == LH_FP32 ? d : d / 2; }
 
-// The natural configuration: four units (16 bytes) per lane, lanes = next power of two.
+// SNAPSHOT's configuration: four units (16 bytes) per lane, lanes = next power of two.
 TileCfg natural_cfg(int dtype, int d)
 {
     const int nu = units_per_row(dtype, d);
@@ -111,16 +111,19 @@ TileCfg natural_cfg(int dtype, int d)
     return c;
 }
 
-// The Hogwild configuration before any tuning or degrees.  Binary32: the natural one.
-// bfloat16 (whose timing runs are switched off): one sample per wavefront, one 4-byte unit
-// per lane over up to 64 lanes (wider rows: more units per lane).  auto_cfg may move a
-// bfloat16 handle to two samples per wavefront once the degrees are known.
+// The Hogwild configuration before any tuning or degrees: one sample per wavefront, one 4-byte
+// unit per lane over up to 64 lanes (wider rows: more units per lane; rows of at most 32 units:
+// as many lanes as units, at least 16).  Spreading a row over lanes rather than over a lane's
+// registers makes each access cover whole lines, and for a given number of samples in flight it
+// spreads them over more wavefronts: with four units a lane over few lanes, binary32 with K = 5
+// and second order took 3.1 against 1.5 ns a sample at d = 16 and 250,000 nodes.  Four workgroups
+// per CU for binary32: eight double the hot set (2^20 nodes, d = 128: 1.81 against 1.51 ns);
+// bfloat16's sixteen are what its registers leave of them.
 TileCfg default_cfg(int dtype, int d)
 {
-    if (dtype == LH_FP32) return natural_cfg(dtype, d);
     const int nu = units_per_row(dtype, d);
     TileCfg c;
-    c.blocks_per_cu = 16;
+    c.blocks_per_cu = dtype == LH_FP32 ? 4 : 16;
     if (nu <= 64) {
         c.lps = next_pow2(nu);
         if (c.lps < 16) c.lps = 16;
@@ -155,10 +158,29 @@ double hogwild_in_flight(const GraphDev &g, int dtype, int orders, const TileCfg
     return hogwild_in_flight_t<uint16_t, 3>(g, c, count, num_cu);
 }
 
+// Binary32 shapes, by the tables' size (see handle.hpp).
+static TileCfg auto_cfg_f32(const lh_handle *h, const TileCfg &wide)
+{
+    const int nu = h->p.d;
+    const double bytes = tables_bytes(h);
+    TileCfg c = wide;
+    if (small_table_window(h->l2_bytes, bytes) > 0.0) {
+        if (nu != 16) c = natural_cfg(h->p.dtype, h->p.d);
+    } else if (nu > 64 && nu <= 128) {  // (64, 2) or (32, 4)
+        if (bytes <= kCachedTableBytes) c = natural_cfg(h->p.dtype, h->p.d);
+    } else if (nu > 32 && nu <= 64) {
+        c.lps = 32;
+        c.upl = 2;
+        c.blocks_per_cu = 8;
+    }
+    return c;
+}
+
 TileCfg auto_cfg(const lh_handle *h)
 {
-    TileCfg one = default_cfg(h->p.dtype, h->p.d);
-    if (h->p.dtype != LH_BF16 || h->p.mode != LH_HOGWILD) return one;
+    const TileCfg one = default_cfg(h->p.dtype, h->p.d);
+    if (h->p.mode != LH_HOGWILD) return one;
+    if (h->p.dtype == LH_FP32) return auto_cfg_f32(h, one);
     TileCfg two = one;
     two.lps = one.lps / 2;
     two.upl = one.upl * 2;

@@ -17,24 +17,29 @@ template <typename TT>
 constexpr int hogwild_min_waves() { return sizeof(TT) == 2 ? 5 : 3; }
 
 // SH: bfloat16 tables whose hot rows live in a binary32 shadow for the launch.  Each
-// wavefront takes 64-sample tiles from the launch's tile counter (g.tiles, zero at launch)
-// until none are left, so wavefronts that meet slow rows do not hold up a fixed share of
-// the work and the grid is only as large as what is resident.
+// wavefront takes tiles of 2^tile_shift samples from the launch's tile counter (g.tiles, zero at
+// launch) until none are left, so wavefronts that meet slow rows do not hold up a fixed share of
+// the work and the grid is only as large as what is resident.  A launch with no more tiles than
+// wavefronts has no counter (g.tiles NULL): wavefront t takes tile t.
 // FULL: the tile shape covers a row exactly (lanes x units == the row's units) and K == KMAX,
 // so row accesses need no bounds mask or slot test.
 template <typename TT, int LPS, int UPL, int KMAX, int ORD, bool SH, bool FULL = false>
 __global__ void __launch_bounds__(256, hogwild_min_waves<TT>()) k_hogwild(GraphDev g, unsigned long long first, unsigned long long end)
 {
     const unsigned lane = threadIdx.x & 63u;
-    const unsigned long long ntiles = (end - first + 63) / 64;
+    const unsigned long long ntiles = ((end - first - 1) >> g.tile_shift) + 1;
+    unsigned long long t = blockIdx.x * 4u + (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     SnapOut so{};
     while (true) {
-        unsigned long long t = 0;
-        if (lane == 0) t = atomicAdd(g.tiles, 1ull);
-        t = ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(t >> 32)) << 32) |
-            (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(t & 0xffffffffull));
+        if (g.tiles) {
+            t = 0;
+            if (lane == 0) t = atomicAdd(g.tiles, 1ull);
+            t = ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(t >> 32)) << 32) |
+                (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(t & 0xffffffffull));
+        }
         if (t >= ntiles) break;
-        sgd_tile<TT, LPS, UPL, KMAX, ORD, false, SH, FULL>(g, first + t * 64, end, so);
+        sgd_tile<TT, LPS, UPL, KMAX, ORD, false, SH, FULL>(g, first + (t << g.tile_shift), end, so, g.tile_shift);
+        if (!g.tiles) break;
     }
 }
 
@@ -57,7 +62,8 @@ __global__ void __launch_bounds__(256) k_snap_contrib(GraphDev g, unsigned long 
         sgd_tile<TT, LPS, UPL, KMAX, ORD, true, false>(g, first + t * 64, end, so);
 }
 
-inline unsigned hogwild_grid(unsigned long long count, int num_cu, int blocks_per_cu)
+// Workgroups of a SNAPSHOT contribution launch: a tile of 64 samples per wavefront.
+inline unsigned snap_grid(unsigned long long count, int num_cu, int blocks_per_cu)
 {
     unsigned long long tiles = (count + 63) / 64;
     unsigned long long blocks = (tiles + 3) / 4;
@@ -91,16 +97,6 @@ inline int hot_heat_for(double W, double hot_rate)
     return (int)t;
 }
 
-// Samples in flight in phase B: resident wavefronts x (64 / LPS) groups.
-template <typename KernelT>
-inline double samples_in_flight(KernelT kernel, unsigned grid, int num_cu, int lps)
-{
-    int occ = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, 256, 0) != hipSuccess || occ < 1) occ = 8;
-    double blocks = std::min<double>((double)grid, (double)num_cu * occ);
-    return blocks * 4.0 * (64.0 / lps);
-}
-
 // (lanes per sample, units per lane) of the Hogwild kernels.
 #define LH_CFG_LIST(X) \
     X(16, 1)           \
@@ -131,34 +127,52 @@ inline double samples_in_flight(KernelT kernel, unsigned grid, int num_cu, int l
     X(64, 4)                \
     X(64, 8)
 
-// The grid of one Hogwild launch over `count` samples and the samples it keeps in flight:
-// the configuration's grid, lowered if the graph's staleness cap asks for fewer.
+// The grid and the tile of one Hogwild launch over `count` samples (at least 1) and the samples
+// it keeps in flight: the configuration's grid, lowered if the graph's caps ask for fewer.
+// narrow: binary32 rows of 16 units, one per lane (kSmallTableCapShare).
+//
+// Tiles have 64 samples, one per lane of phase A; a launch too short to give every wavefront
+// such a tile takes smaller ones, down to four rounds of phase B (below that phase A, which costs
+// the same for any number of samples, is most of a tile's time).
+struct HogwildPlan {
+    unsigned grid = 1;
+    int tile_shift = 6;
+    bool counter = true;  // more tiles than wavefronts
+    double in_flight = 0.0;
+};
+
 template <typename KernelT>
-inline double plan_launch(KernelT kern, int lps, const GraphDev &g, const TileCfg &c, unsigned long long count,
-                          int num_cu, unsigned *grid_out)
+inline HogwildPlan plan_launch(KernelT kern, int lps, bool narrow, const GraphDev &g, const TileCfg &c,
+                               unsigned long long count, int num_cu)
 {
-    unsigned grid = std::min(hogwild_grid(count, num_cu, c.blocks_per_cu), resident_blocks(kern, num_cu));
-    double F = samples_in_flight(kern, grid, num_cu, lps);
-    if (g.max_in_flight > 0.0 && F > g.max_in_flight) {
-        double per_block = 4.0 * (64.0 / lps);
-        grid = (unsigned)std::max(1.0, std::floor(g.max_in_flight / per_block));
-        F = samples_in_flight(kern, grid, num_cu, lps);
-    }
-    *grid_out = grid;
-    return F;
+    HogwildPlan p;
+    const unsigned resident = resident_blocks(kern, num_cu);
+    unsigned most_blocks = std::min((unsigned)num_cu * (unsigned)(c.blocks_per_cu > 0 ? c.blocks_per_cu : 8), resident);
+    const double per_block = 4.0 * (64.0 / lps);
+    double most = g.max_in_flight;
+    if (narrow && std::isinf(g.resid) && g.staleness > 0.0) most = std::min(most, g.staleness * kSmallTableCapShare);
+    if (most > 0.0) most_blocks = std::min(most_blocks, (unsigned)std::max(1.0, std::floor(std::min(most / per_block, 1e9))));
+    const int gpw_shift = 6 - __builtin_ctz((unsigned)lps);
+    const int least = std::min(6, gpw_shift + 2);
+    while (p.tile_shift > least && ((count - 1) >> p.tile_shift) + 1 < 4ull * most_blocks) --p.tile_shift;
+    const unsigned long long tiles = ((count - 1) >> p.tile_shift) + 1;
+    p.grid = (unsigned)std::min<unsigned long long>(most_blocks, (tiles + 3) / 4);
+    p.counter = tiles > 4ull * p.grid;
+    p.in_flight = (double)std::min(p.grid, resident) * per_block;
+    return p;
 }
 
 // One Hogwild launch with the heat threshold for its concurrency.  With a shadow context
 // (bfloat16 tables) the hot rows move into the binary32 shadow for the launch and back
 // afterwards; without one no row is read from a shadow.
 template <typename KernelT>
-hipError_t launch_one(KernelT kern, int lps, const GraphDev &g, const TileCfg &c, unsigned long long first,
+hipError_t launch_one(KernelT kern, int lps, bool narrow, const GraphDev &g, const TileCfg &c, unsigned long long first,
                       unsigned long long end, int num_cu, const ShadowCtx *sc, hipStream_t s)
 {
-    unsigned grid = 0;
-    const double F = plan_launch(kern, lps, g, c, end - first, num_cu, &grid);
+    const HogwildPlan p = plan_launch(kern, lps, narrow, g, c, end - first, num_cu);
     GraphDev gl = g;
-    gl.hot_heat = hot_heat_for(F + g.resid, g.hot_rate);
+    gl.hot_heat = hot_heat_for(p.in_flight + g.resid, g.hot_rate);
+    gl.tile_shift = p.tile_shift;
     if (sc) {
         hipError_t e = shadow_begin(*sc, gl.hot_heat, s);
         if (e != hipSuccess) return e;
@@ -166,11 +180,18 @@ hipError_t launch_one(KernelT kern, int lps, const GraphDev &g, const TileCfg &c
         gl.slot = nullptr;
     }
     if (!gl.tiles) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_zero_tiles<1>, dim3(1), dim3(64), 0, s, gl.tiles);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, gl, first, end);
+    if (p.counter) hipLaunchKernelGGL(k_zero_tiles<1>, dim3(1), dim3(64), 0, s, gl.tiles);
+    else gl.tiles = nullptr;
+    hipLaunchKernelGGL(kern, dim3(p.grid), dim3(256), 0, s, gl, first, end);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && sc) e = shadow_end(*sc, gl.hot_heat, first, s);
     return e;
+}
+
+template <typename TT>
+inline bool narrow_groups(const TileCfg &c)
+{
+    return sizeof(TT) == 4 && c.lps == 16 && c.upl == 1;
 }
 
 // Samples a Hogwild launch of `count` samples would keep in flight (0: no such kernel);
@@ -178,13 +199,13 @@ hipError_t launch_one(KernelT kern, int lps, const GraphDev &g, const TileCfg &c
 template <typename TT, int ORD, bool SH>
 double hogwild_in_flight_sh(const GraphDev &g, const TileCfg &c, unsigned long long count, int num_cu)
 {
-    unsigned grid = 0;
+    const bool nar = narrow_groups<TT>(c);
 #define LH_PLAN_H(L, C)                                                                                  \
     if (c.lps == L && c.upl == C) {                                                                      \
         if (!SH && g.K == 5 && L * C == g.nunits)                                                        \
-            return plan_launch(k_hogwild<TT, L, C, 5, ORD, false, true>, L, g, c, count, num_cu, &grid);   \
-        return plan_launch(g.K <= 5 ? k_hogwild<TT, L, C, 5, ORD, SH> : k_hogwild<TT, L, C, 8, ORD, SH>, L, g, c, \
-                           count, num_cu, &grid);                                                        \
+            return plan_launch(k_hogwild<TT, L, C, 5, ORD, false, true>, L, nar, g, c, count, num_cu).in_flight; \
+        return plan_launch(g.K <= 5 ? k_hogwild<TT, L, C, 5, ORD, SH> : k_hogwild<TT, L, C, 8, ORD, SH>, L, nar, g, c, \
+                           count, num_cu).in_flight;                                                     \
     }
     LH_CFG_LIST(LH_PLAN_H)
 #undef LH_PLAN_H
@@ -203,13 +224,13 @@ template <typename TT, int ORD, bool SH>
 hipError_t launch_hogwild_sh(const GraphDev &g, const TileCfg &c, unsigned long long first, unsigned long long end,
                              int num_cu, const ShadowCtx *sc, hipStream_t s)
 {
-    const bool k5 = g.K <= 5;
+    const bool k5 = g.K <= 5, nar = narrow_groups<TT>(c);
 #define LH_LAUNCH_H(L, C)                                                                        \
     if (c.lps == L && c.upl == C) {                                                              \
         if (!SH && g.K == 5 && L * C == g.nunits)                                                \
-            return launch_one(k_hogwild<TT, L, C, 5, ORD, false, true>, L, g, c, first, end, num_cu, sc, s); \
-        if (k5) return launch_one(k_hogwild<TT, L, C, 5, ORD, SH>, L, g, c, first, end, num_cu, sc, s); \
-        return launch_one(k_hogwild<TT, L, C, 8, ORD, SH>, L, g, c, first, end, num_cu, sc, s);        \
+            return launch_one(k_hogwild<TT, L, C, 5, ORD, false, true>, L, nar, g, c, first, end, num_cu, sc, s); \
+        if (k5) return launch_one(k_hogwild<TT, L, C, 5, ORD, SH>, L, nar, g, c, first, end, num_cu, sc, s); \
+        return launch_one(k_hogwild<TT, L, C, 8, ORD, SH>, L, nar, g, c, first, end, num_cu, sc, s);        \
     }
     LH_CFG_LIST(LH_LAUNCH_H)
 #undef LH_LAUNCH_H
@@ -231,7 +252,7 @@ hipError_t launch_snap_t(const GraphDev &g, const TileCfg &c, unsigned long long
                          int num_cu, const SnapOut &so, hipStream_t s)
 {
     const bool k5 = g.K <= 5;
-    dim3 grid(hogwild_grid(end - first, num_cu, 8)), block(256);
+    dim3 grid(snap_grid(end - first, num_cu, 8)), block(256);
 #define LH_LAUNCH_S(L, C)                                                                              \
     if (c.lps == L && c.upl == C) {                                                                    \
         if (k5)                                                                                        \

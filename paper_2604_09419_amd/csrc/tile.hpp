@@ -1,7 +1,7 @@
 // The per-sample body of LINE edge-sampled SGD on gfx950, shared by the single-graph
 // Hogwild kernels, the SNAPSHOT contribution kernel and the batched persistent kernel.
 //
-// One wavefront handles a tile of 64 consecutive sample indices:
+// One wavefront handles a tile of 64 consecutive sample indices (fewer in short launches):
 //   phase A  lane l draws sample (tile + l): 1 + K Philox4x64-10 blocks, one 32-byte
 //            edge record and K 16-byte negative records (Algorithm 3 root edge,
 //            Eq. (1) negatives), a bit mask of rows repeated inside the tuple and a bit
@@ -532,12 +532,11 @@ __device__ __forceinline__ void sgd_order(const GraphDev &g, int u, const int (&
         }
 #pragma unroll
         for (int j = 0; j <= KMAX; ++j) {
-            if (j > K) break;
             float *brow = crow + (unsigned long long)(j + 1) * d;
 #pragma unroll
             for (int k = 0; k < UPL; ++k) {
                 const int un = k * LPS + gl;
-                if (un < nu) {
+                if (j <= K && un < nu) {
 #pragma unroll
                     for (int e = 0; e < EPU; ++e) brow[un * EPU + e] = gj[j] * val<TT>(a[k], e) - el * val<TT>(b[j][k], e);
                 }
@@ -548,7 +547,7 @@ __device__ __forceinline__ void sgd_order(const GraphDev &g, int u, const int (&
             so.vals[e0] = (uint32_t)e0;
 #pragma unroll
             for (int j = 0; j <= KMAX; ++j) {
-                if (j > K) break;
+                if (j > K) continue;
                 so.keys[e0 + 1 + j] = (uint32_t)((long long)tabB * g.n + ids[j]);
                 so.vals[e0 + 1 + j] = (uint32_t)(e0 + 1 + j);
             }
@@ -571,24 +570,26 @@ __device__ __forceinline__ void sgd_order(const GraphDev &g, int u, const int (&
         // context rows
 #pragma unroll
         for (int j = 0; j <= KMAX; ++j) {
-            if (!FULL && j > K) break;
-            float inc[UPL][EPU];
+            if (FULL || j <= K) {  // (a break would keep the loop, and so b in memory)
+                float inc[UPL][EPU];
 #pragma unroll
-            for (int k = 0; k < UPL; ++k)
+                for (int k = 0; k < UPL; ++k)
 #pragma unroll
-                for (int e = 0; e < EPU; ++e) inc[k][e] = gj[j] * val<TT>(a[k], e) - el * val<TT>(b[j][k], e);
-            write_row<TT, LPS, UPL, SH, FULL>(g, tabB, ids[j], gl, b[j], inc, (atom & (2u << j)) != 0,
-                                        seed + (uint32_t)(j + 2) * kSlot);
+                    for (int e = 0; e < EPU; ++e) inc[k][e] = gj[j] * val<TT>(a[k], e) - el * val<TT>(b[j][k], e);
+                write_row<TT, LPS, UPL, SH, FULL>(g, tabB, ids[j], gl, b[j], inc, (atom & (2u << j)) != 0,
+                                                  seed + (uint32_t)(j + 2) * kSlot);
+            }
         }
     }
 }
 
-// One tile of 64 samples [tile, min(tile + 64, end)).  UPL units per lane.  SH: bfloat16
+// One tile of samples [tile, min(tile + 2^tile_shift, end)), at most 64 and a multiple of the
+// groups per wavefront.  UPL units per lane.  SH: bfloat16
 // Hogwild with a binary32 shadow of the hot rows (compiled out otherwise: the shadow's
 // address choice and second-half loads cost a quarter of the kernel's speed even unused).
 template <typename TT, int LPS, int UPL, int KMAX, int ORD, bool SNAP, bool SH, bool FULL = false>
 __device__ __forceinline__ void sgd_tile(const GraphDev &g, unsigned long long tile, unsigned long long end,
-                                         const SnapOut &so)
+                                         const SnapOut &so, int tile_shift = 6)
 {
     static_assert(LPS >= 1 && LPS <= 64 && (64 % LPS) == 0, "lanes per sample divide the wavefront");
     constexpr int GPW = 64 / LPS;
@@ -605,7 +606,7 @@ __device__ __forceinline__ void sgd_tile(const GraphDev &g, unsigned long long t
     for (int j = 0; j <= KMAX; ++j) my_ids[j] = 0;
     {
         const unsigned long long s = tile + (unsigned long long)lane;
-        if (s < end) {
+        if (s < end && (lane >> tile_shift) == 0) {
             // One Philox block at a time, its record load issued at once, so the loads of
             // all 1 + K slots are in flight together while the blocks are not interleaved
             // (which would hold 1 + K blocks of state in registers).
@@ -643,11 +644,12 @@ __device__ __forceinline__ void sgd_tile(const GraphDev &g, unsigned long long t
             // high half: slots whose row is the vertex row u
 #pragma unroll
             for (int j = 0; j <= KMAX; ++j) {
-                if (j > K) break;
-                if (my_ids[j] == my_u) my_dup |= 1u << (16 + j);
+                if (j <= K) {
+                    if (my_ids[j] == my_u) my_dup |= 1u << (16 + j);
 #pragma unroll
-                for (int jj = 0; jj < j; ++jj)
-                    if (my_ids[jj] == my_ids[j]) my_dup |= (1u << j) | (1u << jj);
+                    for (int jj = 0; jj < j; ++jj)
+                        if (my_ids[jj] == my_ids[j]) my_dup |= (1u << j) | (1u << jj);
+                }
             }
             // bfloat16 Hogwild with a shadow: the rows with a shadow slot are this launch's
             // hot rows; their ids become ~slot (negative, so equal rows stay equal and never
@@ -675,7 +677,8 @@ __device__ __forceinline__ void sgd_tile(const GraphDev &g, unsigned long long t
     }
 
     // ---- phase B: LPS lanes per sample ----------------------------------------
-    for (int r = 0; r < LPS; ++r) {
+    const int rounds = (1 << tile_shift) / GPW;
+    for (int r = 0; r < rounds; ++r) {
         const int src = r * GPW + grp;
         const int u = sample_lane<LPS>(my_u, src);
         int ids[KMAX + 1];
