@@ -242,7 +242,6 @@ __global__ void __launch_bounds__(256, (batch_min_waves<TT, SH>())) k_batch(Batc
 {
     using Cfg = BatchCfg<TT, V>;
     const int lane = threadIdx.x & 63;
-    SnapOut so{};
     while (true) {
         unsigned long long item = 0;
         if (lane == 0) item = atomicAdd(a.queue, 1ull);
@@ -262,13 +261,13 @@ __global__ void __launch_bounds__(256, (batch_min_waves<TT, SH>())) k_batch(Batc
         const bool kfull = g.K == KMAX;
         if (kfull && g.nunits == Cfg::LS * Cfg::US) {
             for (unsigned long long t = s0; t < s1; t += 64)
-                sgd_tile<TT, Cfg::LS, Cfg::US, KMAX, 2, false, SH, true>(g, t, s1, so);
+                sgd_tile<TT, Cfg::LS, Cfg::US, KMAX, 2, SH, true>(g, t, s1);
         } else if (kfull && g.nunits == Cfg::LL * Cfg::UL) {
             for (unsigned long long t = s0; t < s1; t += 64)
-                sgd_tile<TT, Cfg::LL, Cfg::UL, KMAX, 2, false, SH, true>(g, t, s1, so);
+                sgd_tile<TT, Cfg::LL, Cfg::UL, KMAX, 2, SH, true>(g, t, s1);
         } else {
             for (unsigned long long t = s0; t < s1; t += 64)
-                sgd_tile<TT, Cfg::LL, Cfg::UL, KMAX, 2, false, SH>(g, t, s1, so);
+                sgd_tile<TT, Cfg::LL, Cfg::UL, KMAX, 2, SH>(g, t, s1);
         }
         if (lane == 0 && s1 > s0) atomicAdd(&a.done[lo], s1 - s0);
     }

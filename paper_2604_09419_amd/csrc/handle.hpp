@@ -81,9 +81,8 @@ struct WsLayout {
     size_t nheat = 0;                                   // [n] bytes: per-node heat
     size_t slot = 0, srows = 0, shadow = 0;             // bfloat16 Hogwild shadow (else 0)
     long long shadow_cap = 0;                           // shadow rows per table
-    size_t keys0 = 0, keys1 = 0, vals0 = 0, vals1 = 0, contrib = 0, hist = 0, ilev = 0,
-           seg = 0, segid = 0, total = 0;
-    long long entries = 0, hist_n = 0, ilev_n = 0;
+    size_t keys0 = 0, keys1 = 0, keys2 = 0, vals0 = 0, vals1 = 0, contrib = 0, hist = 0, part = 0;  // SNAPSHOT
+    size_t total = 0;
 };
 
 // Scratch of the alias build ([k]: 0 the negative table, 1 the edge table).
@@ -138,10 +137,6 @@ constexpr size_t kNoAllocScratchBytes = 65ull << 20;
 constexpr long long kNoAllocMaxItems = 1ll << 21;  // largest n and largest m it accepts
 // Look up that array's device address on `device` (current) once; lh_create calls it.
 hipError_t noalloc_scratch_setup(int device);
-
-constexpr int RADIX_ITEMS = 16;
-constexpr int RADIX_THREADS = 256;
-constexpr int RADIX_TILE = RADIX_ITEMS * RADIX_THREADS;
 
 }  // namespace lh
 
@@ -261,11 +256,4 @@ lh_status train_snapshot(lh_handle *h, unsigned long long first, unsigned long l
 lh_status walk_each_chunk(lh_handle *h, unsigned long long first, unsigned long long count,
                           const std::function<lh_status(unsigned long long, unsigned long long, const int2 *,
                                                         unsigned long long)> &body);
-// Stable LSD radix sort of (keys, values) on the low `bits` bits of the keys, 4-bit digits,
-// each thread ranking its items in order (so equal keys keep their input order).  ka/va
-// hold the input, kb/vb are the other buffers of the ping-pong; *kout/*vout receive the
-// buffers that hold the result.  hist: 16 * ceil(E / RADIX_TILE) words; ilev: the scan
-// levels of that many words.  E < 2^32.
-void radix_sort_u32(uint32_t *ka, uint32_t *va, uint32_t *kb, uint32_t *vb, long long E, int bits, uint32_t *hist,
-                    uint32_t *ilev, hipStream_t s, uint32_t **kout, uint32_t **vout);
 }  // namespace lh

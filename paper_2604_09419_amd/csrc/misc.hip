@@ -3,6 +3,7 @@
 #include "handle.hpp"
 #include "scan.hpp"
 #include "sgd_kernels.hpp"
+#include "sort.hpp"
 
 namespace lh {
 
@@ -42,19 +43,14 @@ WsLayout ws_layout(const lh_params &p, long long n, long long m)
     if (p.mode == LH_SNAPSHOT) {
         long long nord = p.orders == 3 ? 2 : 1;
         long long E = p.batch * nord * (long long)(p.K + 2);
-        L.entries = E;
         L.keys0 = carve(off, 4 * (size_t)E);
         L.keys1 = carve(off, 4 * (size_t)E);
+        L.keys2 = carve(off, 4 * (size_t)E);
         L.vals0 = carve(off, 4 * (size_t)E);
         L.vals1 = carve(off, 4 * (size_t)E);
         L.contrib = carve(off, 4 * (size_t)E * (size_t)p.d);
-        L.hist_n = 16 * LH_CDIV(E, RADIX_TILE);
-        L.hist = carve(off, 4 * (size_t)L.hist_n);
-        long long mx = L.hist_n > E ? L.hist_n : E;
-        L.ilev_n = scan_levels_size(mx);
-        L.ilev = carve(off, 4 * (size_t)L.ilev_n);
-        L.seg = carve(off, 4 * (size_t)(E + 1));
-        L.segid = carve(off, 4 * (size_t)(E + 1));
+        L.hist = carve(off, 4 * (size_t)sort_hist_size(E));
+        L.part = carve(off, 4 * (size_t)sort_part_size(E));
     }
     L.total = off;
     return L;

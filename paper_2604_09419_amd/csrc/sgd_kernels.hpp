@@ -1,5 +1,4 @@
-// Hogwild and SNAPSHOT-contribution kernels over a range of sample indices, and their
-// host launchers.  Each (dtype, orders) pair is instantiated in its own translation
+// Hogwild kernels over a range of sample indices, and their host launchers.  Each (dtype, orders) pair is instantiated in its own translation
 // unit so the kernel variants compile in parallel.
 #pragma once
 
@@ -29,7 +28,6 @@ __global__ void __launch_bounds__(256, hogwild_min_waves<TT>()) k_hogwild(GraphD
     const unsigned lane = threadIdx.x & 63u;
     const unsigned long long ntiles = ((end - first - 1) >> g.tile_shift) + 1;
     unsigned long long t = blockIdx.x * 4u + (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    SnapOut so{};
     while (true) {
         if (g.tiles) {
             t = 0;
@@ -38,7 +36,7 @@ __global__ void __launch_bounds__(256, hogwild_min_waves<TT>()) k_hogwild(GraphD
                 (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(t & 0xffffffffull));
         }
         if (t >= ntiles) break;
-        sgd_tile<TT, LPS, UPL, KMAX, ORD, false, SH, FULL>(g, first + (t << g.tile_shift), end, so, g.tile_shift);
+        sgd_tile<TT, LPS, UPL, KMAX, ORD, SH, FULL>(g, first + (t << g.tile_shift), end, g.tile_shift);
         if (!g.tiles) break;
     }
 }
@@ -48,29 +46,6 @@ template <int N>
 __global__ void k_zero_tiles(unsigned long long *c)
 {
     if (threadIdx.x < N) c[threadIdx.x] = 0ull;
-}
-
-template <typename TT, int LPS, int UPL, int KMAX, int ORD>
-__global__ void __launch_bounds__(256) k_snap_contrib(GraphDev g, unsigned long long first, unsigned long long end,
-                                                      SnapOut so)
-{
-    const unsigned wpb = blockDim.x >> 6;
-    unsigned long long wave = (unsigned long long)blockIdx.x * wpb + (threadIdx.x >> 6);
-    unsigned long long nw = (unsigned long long)gridDim.x * wpb;
-    unsigned long long ntiles = (end - first + 63) / 64;
-    for (unsigned long long t = wave; t < ntiles; t += nw)
-        sgd_tile<TT, LPS, UPL, KMAX, ORD, true, false>(g, first + t * 64, end, so);
-}
-
-// Workgroups of a SNAPSHOT contribution launch: a tile of 64 samples per wavefront.
-inline unsigned snap_grid(unsigned long long count, int num_cu, int blocks_per_cu)
-{
-    unsigned long long tiles = (count + 63) / 64;
-    unsigned long long blocks = (tiles + 3) / 4;
-    unsigned long long cap = (unsigned long long)num_cu * (unsigned long long)(blocks_per_cu > 0 ? blocks_per_cu : 8);
-    if (blocks > cap) blocks = cap;
-    if (blocks < 1) blocks = 1;
-    return (unsigned)blocks;
 }
 
 // Resident workgroups of a kernel on the device (at least 1 per CU).
@@ -115,16 +90,6 @@ inline int hot_heat_for(double W, double hot_rate)
     X(8, 8)            \
     X(16, 8)           \
     X(32, 8)           \
-    X(64, 8)
-
-// SNAPSHOT contributions use only the natural configuration of each width.
-#define LH_SNAP_CFG_LIST(X) \
-    X(2, 4)                 \
-    X(4, 4)                 \
-    X(8, 4)                 \
-    X(16, 4)                \
-    X(32, 4)                \
-    X(64, 4)                \
     X(64, 8)
 
 // The grid and the tile of one Hogwild launch over `count` samples (at least 1) and the samples
@@ -247,38 +212,15 @@ hipError_t launch_hogwild_t(const GraphDev &g, const TileCfg &c, unsigned long l
     return launch_hogwild_sh<TT, ORD, false>(g, c, first, end, num_cu, nullptr, s);
 }
 
-template <typename TT, int ORD>
-hipError_t launch_snap_t(const GraphDev &g, const TileCfg &c, unsigned long long first, unsigned long long end,
-                         int num_cu, const SnapOut &so, hipStream_t s)
-{
-    const bool k5 = g.K <= 5;
-    dim3 grid(snap_grid(end - first, num_cu, 8)), block(256);
-#define LH_LAUNCH_S(L, C)                                                                              \
-    if (c.lps == L && c.upl == C) {                                                                    \
-        if (k5)                                                                                        \
-            hipLaunchKernelGGL((k_snap_contrib<TT, L, C, 5, ORD>), grid, block, 0, s, g, first, end, so); \
-        else                                                                                           \
-            hipLaunchKernelGGL((k_snap_contrib<TT, L, C, 8, ORD>), grid, block, 0, s, g, first, end, so); \
-        return hipGetLastError();                                                                      \
-    }
-    LH_SNAP_CFG_LIST(LH_LAUNCH_S)
-#undef LH_LAUNCH_S
-    return hipErrorInvalidConfiguration;
-}
-
 // Explicit instantiations live in sgd_<dtype>_o<orders>.hip.
 #define LH_DECLARE_LAUNCHERS(TT, ORD)                                                                          \
     extern template hipError_t launch_hogwild_t<TT, ORD>(const GraphDev &, const TileCfg &, unsigned long long, \
                                                          unsigned long long, int, const ShadowCtx *, hipStream_t); \
-    extern template hipError_t launch_snap_t<TT, ORD>(const GraphDev &, const TileCfg &, unsigned long long,    \
-                                                      unsigned long long, int, const SnapOut &, hipStream_t); \
     extern template double hogwild_in_flight_t<TT, ORD>(const GraphDev &, const TileCfg &, unsigned long long, int);
 
 #define LH_DEFINE_LAUNCHERS(TT, ORD)                                                                    \
     template hipError_t launch_hogwild_t<TT, ORD>(const GraphDev &, const TileCfg &, unsigned long long, \
                                                   unsigned long long, int, const ShadowCtx *, hipStream_t); \
-    template hipError_t launch_snap_t<TT, ORD>(const GraphDev &, const TileCfg &, unsigned long long,    \
-                                               unsigned long long, int, const SnapOut &, hipStream_t); \
     template double hogwild_in_flight_t<TT, ORD>(const GraphDev &, const TileCfg &, unsigned long long, int);
 
 }  // namespace lh

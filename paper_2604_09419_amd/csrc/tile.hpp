@@ -1,5 +1,6 @@
 // The per-sample body of LINE edge-sampled SGD on gfx950, shared by the single-graph
-// Hogwild kernels, the SNAPSHOT contribution kernel and the batched persistent kernel.
+// Hogwild kernels and the batched persistent kernel, and the draws, which the SNAPSHOT kernels
+// use too.
 //
 // One wavefront handles a tile of 64 consecutive sample indices (fewer in short launches):
 //   phase A  lane l draws sample (tile + l): 1 + K Philox4x64-10 blocks, one 32-byte
@@ -11,8 +12,7 @@
 //            group holds units gl, gl + LPS, gl + 2 LPS, ... so every load, store and
 //            atomic instruction of the group covers LPS consecutive units.  The 1 + K
 //            dot products are reduced across the group with DPP, and the updates of
-//            Algorithm 1 / Eqs. (2)-(3) are written back (HOGWILD) or emitted as
-//            per-row contributions (SNAPSHOT, Eq. (4)).
+//            Algorithm 1 / Eqs. (2)-(3) are written back .
 //
 // HOGWILD write-back: a cold row is stored (row as loaded plus the sample's increment;
 // no locks) with a system-scope store (binary32 rows of a one-sample wavefront: a
@@ -44,30 +44,7 @@ struct Elem<uint16_t> {
     static constexpr int EPU = 2;
 };
 
-// ---- one 4-byte unit ----------------------------------------------------------------
-template <typename TT>
-__device__ __forceinline__ void unit_to_f32(uint32_t w, float (&o)[Elem<TT>::EPU])
-{
-    if constexpr (sizeof(TT) == 4) {
-        o[0] = __uint_as_float(w);
-    } else {
-        o[0] = __uint_as_float(w << 16);
-        o[1] = __uint_as_float(w & 0xffff0000u);
-    }
-}
-
-// Pack a unit's values; bfloat16 with stochastic rounding from 32 random bits.
-template <typename TT>
-__device__ __forceinline__ uint32_t f32_to_unit(const float (&x)[Elem<TT>::EPU], uint32_t rnd)
-{
-    if constexpr (sizeof(TT) == 4) {
-        return __float_as_uint(x[0]);
-    } else {
-        return bf16x2_sr(x[0], x[1], rnd);
-    }
-}
-
-// ---- drawing one sample (shared by the parity hook k_sample and phase A) ------------
+// ---- drawing one sample (shared by k_sample, k_snap_draw and phase A) ---------------
 // Slot j of sample s (0: the positive arc, Algorithm 3's root edge; 1..K: negatives of
 // Eq. (1), Algorithm 1) uses Philox4x64-10 block (key (seed, graph_id), counter
 // (s, j, 0, 0)): column floor(x0 N / 2^64), kept when x1 < thr[column], else its alias.
@@ -156,15 +133,6 @@ __device__ __forceinline__ bool neg_pick(const uint4 &nr, const SlotDraw &d, int
     id = keep ? (int)d.col : (int)nr.z;
     return keep;
 }
-
-// Where SNAPSHOT contributions go.
-struct SnapOut {
-    uint32_t *keys;           // [entries]  table * n + row
-    uint32_t *vals;           // [entries]  entry index
-    float *contrib;           // [entries x d], binary32
-    unsigned long long base;  // first sample of the batch
-    int nord;                 // orders per sample (1 or 2)
-};
 
 // Sum over an aligned group of LPS lanes, every lane receiving the sum.  Within a row
 // of 16 lanes the butterfly uses DPP: quad_perm [1,0,3,2] and [2,3,0,1] (xor 1, 2), then
@@ -455,14 +423,13 @@ __device__ __forceinline__ void write_row(const GraphDev &g, int t, int id, int 
 // the context rows (the same table for first order).  ids[0] = v, ids[1..K] = negatives
 // (bfloat16 Hogwild: ~slot for rows in the shadow).  hot: bit 0 for the vertex row,
 // bit 1 + j for slot j.
-template <typename TT, int LPS, int UPL, int KMAX, bool FIRST, bool SNAP, bool SH, bool FULL>
+template <typename TT, int LPS, int UPL, int KMAX, bool FIRST, bool SH, bool FULL>
 __device__ __forceinline__ void sgd_order(const GraphDev &g, int u, const int (&ids)[KMAX + 1], int K, float eta,
-                                          unsigned dupb, unsigned dupu, unsigned hot, uint32_t sr, int oi, int gl,
-                                          const SnapOut &so, unsigned long long s, int tabA, int tabB,
+                                          unsigned dupb, unsigned dupu, unsigned hot, uint32_t sr, int gl, int tabA,
+                                          int tabB,
                                           const Rows<TT, UPL, KMAX> &rows)
 {
     constexpr int EPU = Elem<TT>::EPU;
-    const int d = g.d, nu = g.nunits;
     const auto &a = rows.a;
     const auto &b = rows.b;
     float gj[KMAX + 1];
@@ -517,43 +484,7 @@ __device__ __forceinline__ void sgd_order(const GraphDev &g, int u, const int (&
             dA[k][e] = acc;
         }
 
-    if constexpr (SNAP) {
-        // Entries of this sample/order: slot 0 = A[u] (dA), slot 1 + j = B[ids[j]] (delta_j).
-        const unsigned long long e0 =
-            ((s - so.base) * (unsigned long long)so.nord + (unsigned long long)oi) * (unsigned long long)(K + 2);
-        float *crow = so.contrib + e0 * (unsigned long long)d;
-#pragma unroll
-        for (int k = 0; k < UPL; ++k) {
-            const int un = k * LPS + gl;
-            if (un < nu) {
-#pragma unroll
-                for (int e = 0; e < EPU; ++e) crow[un * EPU + e] = dA[k][e];
-            }
-        }
-#pragma unroll
-        for (int j = 0; j <= KMAX; ++j) {
-            float *brow = crow + (unsigned long long)(j + 1) * d;
-#pragma unroll
-            for (int k = 0; k < UPL; ++k) {
-                const int un = k * LPS + gl;
-                if (j <= K && un < nu) {
-#pragma unroll
-                    for (int e = 0; e < EPU; ++e) brow[un * EPU + e] = gj[j] * val<TT>(a[k], e) - el * val<TT>(b[j][k], e);
-                }
-            }
-        }
-        if (gl == 0) {
-            so.keys[e0] = (uint32_t)((long long)tabA * g.n + u);
-            so.vals[e0] = (uint32_t)e0;
-#pragma unroll
-            for (int j = 0; j <= KMAX; ++j) {
-                if (j > K) continue;
-                so.keys[e0 + 1 + j] = (uint32_t)((long long)tabB * g.n + ids[j]);
-                so.vals[e0 + 1 + j] = (uint32_t)(e0 + 1 + j);
-            }
-        }
-        return;
-    } else {
+    {
         // A row that occurs more than once in this order of the sample (two slots with
         // one row, or in first order a slot equal to the vertex row) takes the atomic
         // path at every occurrence: each occurrence adds its own increment, computed from
@@ -564,7 +495,6 @@ __device__ __forceinline__ void sgd_order(const GraphDev &g, int u, const int (&
         uint32_t seed = 0u;
         if constexpr (EPU == 2) seed = lowbias32(sr);
         constexpr uint32_t kSlot = 0x632BE59Bu;
-        (void)oi;
         // vertex row
         write_row<TT, LPS, UPL, SH, FULL>(g, tabA, u, gl, a, dA, (atom & 1u) != 0, seed + kSlot);
         // context rows
@@ -587,9 +517,9 @@ __device__ __forceinline__ void sgd_order(const GraphDev &g, int u, const int (&
 // groups per wavefront.  UPL units per lane.  SH: bfloat16
 // Hogwild with a binary32 shadow of the hot rows (compiled out otherwise: the shadow's
 // address choice and second-half loads cost a quarter of the kernel's speed even unused).
-template <typename TT, int LPS, int UPL, int KMAX, int ORD, bool SNAP, bool SH, bool FULL = false>
+template <typename TT, int LPS, int UPL, int KMAX, int ORD, bool SH, bool FULL = false>
 __device__ __forceinline__ void sgd_tile(const GraphDev &g, unsigned long long tile, unsigned long long end,
-                                         const SnapOut &so, int tile_shift = 6)
+                                         int tile_shift = 6)
 {
     static_assert(LPS >= 1 && LPS <= 64 && (64 % LPS) == 0, "lanes per sample divide the wavefront");
     constexpr int GPW = 64 / LPS;
@@ -654,7 +584,7 @@ __device__ __forceinline__ void sgd_tile(const GraphDev &g, unsigned long long t
             // bfloat16 Hogwild with a shadow: the rows with a shadow slot are this launch's
             // hot rows; their ids become ~slot (negative, so equal rows stay equal and never
             // meet a table id).
-            if constexpr (sizeof(TT) == 2 && !SNAP && SH) {
+            if constexpr (sizeof(TT) == 2 && SH) {
                 if (g.slot) {
                     my_hot = 0;
                     int sl[KMAX + 2];
@@ -685,10 +615,9 @@ __device__ __forceinline__ void sgd_tile(const GraphDev &g, unsigned long long t
 #pragma unroll
         for (int j = 0; j <= KMAX; ++j) ids[j] = sample_lane<LPS>(my_ids[j], src);
         const unsigned dup = (unsigned)sample_lane<LPS>((int)my_dup, src);
-        unsigned hot = 0;
+        const unsigned hot = (unsigned)sample_lane<LPS>((int)my_hot, src);
         uint32_t sr = 0;
-        if constexpr (!SNAP) hot = (unsigned)sample_lane<LPS>((int)my_hot, src);
-        if constexpr (sizeof(TT) == 2 && !SNAP) sr = (uint32_t)sample_lane<LPS>((int)my_sr, src);
+        if constexpr (sizeof(TT) == 2) sr = (uint32_t)sample_lane<LPS>((int)my_sr, src);
         // every cross-lane read before lanes diverge
         const float eta = __int_as_float(sample_lane<LPS>(__float_as_int(my_eta), src));
         const unsigned long long s = tile + (unsigned long long)src;
@@ -701,16 +630,12 @@ __device__ __forceinline__ void sgd_tile(const GraphDev &g, unsigned long long t
             load_rows<TT, LPS, UPL, KMAX, SH, FULL>(r2, g, LH_TABLE_U, LH_TABLE_C, u, ids, K, gl);
         if constexpr ((ORD & 1) != 0)
             load_rows<TT, LPS, UPL, KMAX, SH, FULL>(r1, g, LH_TABLE_U1, LH_TABLE_U1, u, ids, K, gl);
-        int oi = 0;
-        if constexpr ((ORD & 2) != 0) {
-            sgd_order<TT, LPS, UPL, KMAX, false, SNAP, SH, FULL>(g, u, ids, K, eta, dupb, dupu, hot, sr, oi, gl, so, s,
-                                                       LH_TABLE_U, LH_TABLE_C, r2);
-            ++oi;
-        }
-        if constexpr ((ORD & 1) != 0) {
-            sgd_order<TT, LPS, UPL, KMAX, true, SNAP, SH, FULL>(g, u, ids, K, eta, dupb, dupu, hot, sr ^ 0x5bd1e995u, oi, gl,
-                                                      so, s, LH_TABLE_U1, LH_TABLE_U1, r1);
-        }
+        if constexpr ((ORD & 2) != 0)
+            sgd_order<TT, LPS, UPL, KMAX, false, SH, FULL>(g, u, ids, K, eta, dupb, dupu, hot, sr, gl, LH_TABLE_U,
+                                                           LH_TABLE_C, r2);
+        if constexpr ((ORD & 1) != 0)
+            sgd_order<TT, LPS, UPL, KMAX, true, SH, FULL>(g, u, ids, K, eta, dupb, dupu, hot, sr ^ 0x5bd1e995u, gl,
+                                                          LH_TABLE_U1, LH_TABLE_U1, r1);
     }
 }
 
