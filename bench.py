@@ -52,7 +52,8 @@ TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "k_hogwild_c2_fp32_hbm_traffic.
 # SNAPSHOT sources and the other dtype/order units do not enter this kernel.
 KERNEL_SOURCES = [
     "paper_2604_09419_amd/csrc/common.hpp", "paper_2604_09419_amd/csrc/handle.hpp",
-    "paper_2604_09419_amd/csrc/scan.hpp", "paper_2604_09419_amd/csrc/tile.hpp",
+    "paper_2604_09419_amd/csrc/scan.hpp", "paper_2604_09419_amd/csrc/table.hpp",
+    "paper_2604_09419_amd/csrc/tile.hpp",
     "paper_2604_09419_amd/csrc/sgd_kernels.hpp", "paper_2604_09419_amd/csrc/alias.hip",
     "paper_2604_09419_amd/csrc/api.hip", "paper_2604_09419_amd/csrc/misc.hip",
     "paper_2604_09419_amd/csrc/sgd_f32_o3.hip", "include/linehip.h", "paper_2604_09419_amd/build.py",

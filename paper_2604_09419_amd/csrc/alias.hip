@@ -21,7 +21,7 @@
 #include <vector>
 
 #include "handle.hpp"
-#include "scan.hpp"
+#include "table.hpp"
 
 #pragma clang fp contract(off)
 
@@ -345,12 +345,6 @@ __global__ void k_fill_u8(uint8_t *p, long long n, uint8_t v)
     if (i < n) p[i] = v;
 }
 
-__device__ __forceinline__ unsigned long long prob_to_thr(double prob)
-{
-    if (prob >= 1.0) return ~0ull;
-    return (unsigned long long)__dmul_rn(prob, 18446744073709551616.0);
-}
-
 struct RecOut {
     EdgeRec *erec;  // edge table, or
     NegRec *nrec;   // negative table
@@ -386,93 +380,83 @@ __device__ __forceinline__ void write_rec(const RecOut &o, long long i, unsigned
 }
 
 // ---------------------------------------------------------------------------
-// One table's build.  Both tables are built by the same launches: a kernel's first workgroups
-// take table 0, the rest table 1, and every count that a later kernel needs stays on the device,
-// so the host waits once, at the end.  (C2: checks, degrees, both tables and their export 5.46 ms
-// with a table at a time and three waits, 1.23 ms so.)
-//
-// The construction reads its prefix sums only through searches, so no scan is ever written out
-// element by element with its offsets: a scan is the chains' values within each chunk and, per
-// chunk, the offset of the chunk (the canonical scan of the totals before it).  Rounding is
-// monotone, so the running maximum of off + x within a chunk is off + (the running maximum of
-// x), and across chunks it is enough to keep the largest value before the chunk:
-//   value(i) = max(before[c], off[c] + loc[i]),  c = i / 1024.
+// The two tables of the graph (table.hpp).  Both are built by the same launches: a kernel's first
+// workgroups take table 0, the rest table 1, and every count that a later kernel needs stays on
+// the device, so the host waits once, at the end.  (C2: checks, degrees, both tables and their
+// export 5.46 ms with a table at a time and three waits, 1.23 ms so.)
 // ---------------------------------------------------------------------------
-struct Scan {
-    const double *loc;   // [n] per element, within its chunk
-    const double *off;   // [chunks] canonical scan of the totals before the chunk (0 for the first)
-    const double *before;  // [chunks] largest value before the chunk (-inf for the first)
-    const double *end;   // [chunks] value of the chunk's last element
-    long long n;
-
-    __device__ __forceinline__ double at(long long i) const
-    {
-        const long long c = i / SCAN_CHUNK;
-        return __builtin_fmax(before[c], off[c] + loc[i]);
-    }
-};
-
-constexpr int SPLIT_ITEMS = 1024;  // items a wavefront splits
-
-struct Table {
-    long long N;
-    const float *w;        // arc weights, or NULL: the weight of item i is neg_weight(deg[i])
-    const int32_t *deg;
-    double *dx;            // [N] deficits of the lights, then excesses of the heavies
-    int32_t *idx;          // [N] the heavies' items, in index order
-    int32_t *blk;          // [N / 1024 + 2] lights before each 1,024 items; last: all of them
-    double *tot, *mxl;     // [N / 1024 + 2] chunk totals and chunk maxima, then (in place)
-                           // the totals' own chains and the chunks' last values
-    double *off, *before;  // [N / 1024 + 2]
-    double *W;             // total weight
+struct GraphTable : Table {
+    const int32_t *deg;  // without w: the weight of item i is neg_weight(deg[i])
     RecOut out;
 
     __device__ __forceinline__ double weight(long long i) const { return w ? (double)w[i] : neg_weight(deg[i]); }
-    // q_i = fl(fl(w_i N) / W).  A total that is not a positive finite number makes every item
-    // heavy (prob 1, self).
-    __device__ __forceinline__ double q(long long i, double Wt) const
+    __device__ __forceinline__ double q(long long i, double Wt) const { return alias_q(weight(i), N, Wt); }
+    // Items first, first + 64, .., RS of them, those before end.
+    template <int RS>
+    __device__ __forceinline__ void write(long long first, long long end, const unsigned long long (&thr)[RS],
+                                          const uint32_t (&al)[RS]) const
     {
-        return Wt > 0.0 && !isinf(Wt) ? __ddiv_rn(__dmul_rn(weight(i), (double)N), Wt) : 1.0;
-    }
-    __device__ __forceinline__ long long lights() const { return blk[LH_CDIV(N, SPLIT_ITEMS)]; }
-    // The scan of one half (false: lights, true: heavies), its chunks after the lights' ones.
-    __device__ __forceinline__ Scan half(bool heavy, long long nL) const
-    {
-        const long long c0 = heavy ? LH_CDIV(nL, SCAN_CHUNK) : 0;
-        return Scan{dx + (heavy ? nL : 0), off + c0, before + c0, mxl + c0, heavy ? N - nL : nL};
+        if (out.erec) {
+            int32_t e[RS][4];  // endpoints: source and destination, of the item and of its alias
+#pragma unroll
+            for (int r = 0; r < RS; ++r) {
+                const long long i = first + r * 64 < end ? first + r * 64 : end - 1;
+                const long long z = first + r * 64 < end ? (long long)al[r] : end - 1;
+                e[r][0] = out.src[i];
+                e[r][1] = out.dst[i];
+                e[r][2] = out.src[z];
+                e[r][3] = out.dst[z];
+            }
+            uint32_t heat[RS];
+#pragma unroll
+            for (int r = 0; r < RS; ++r)
+                heat[r] = (uint32_t)out.heat[e[r][0]] | ((uint32_t)out.heat[e[r][1]] << 8) |
+                          ((uint32_t)out.heat[e[r][2]] << 16) | ((uint32_t)out.heat[e[r][3]] << 24);
+#pragma unroll
+            for (int r = 0; r < RS; ++r)
+                if (first + r * 64 < end)
+                    out.erec[first + r * 64] = EdgeRec{thr[r], (int32_t)al[r], e[r][0], e[r][1], e[r][2], e[r][3], heat[r]};
+        } else {
+#pragma unroll
+            for (int r = 0; r < RS; ++r)
+                if (first + r * 64 < end) write_rec(out, first + r * 64, thr[r], (int32_t)al[r]);
+        }
     }
 };
 
 struct Tables {
-    Table t[2];
+    GraphTable t[2];
     unsigned first[3];  // workgroups [first[k], first[k + 1]) take table k
-};
 
-__device__ __forceinline__ const Table &table_of(const Tables &T, long long &b)
-{
-    const int k = blockIdx.x >= T.first[1] ? 1 : 0;
-    b = (long long)blockIdx.x - T.first[k];
-    return T.t[k];
-}
+    __device__ __forceinline__ const GraphTable &of(long long &b) const
+    {
+        const int k = blockIdx.x >= first[1] ? 1 : 0;
+        b = (long long)blockIdx.x - first[k];
+        return t[k];
+    }
+    __device__ __forceinline__ const GraphTable &whole(unsigned k) const { return t[k]; }
+};
 
 // Chains over the weights, of which only the total is needed: no element is stored.  The node
 // weights are in dx (k_neg_weights), which the split overwrites later.
 __global__ void __launch_bounds__(256) k_chain_weights(Tables T)
 {
     __shared__ double lds[CHAIN_LDS];
+    __shared__ ChainSegs segs;
     long long b;
-    const Table &t = table_of(T, b);
+    const GraphTable &t = T.of(b);
     const long long c0 = b * WAVE_CHUNKS, N = t.N;
-    const int tiles = chain_tiles(N - c0 * SCAN_CHUNK);
+    chunk_segs(segs, c0, N);
+    __syncthreads();
     const float *w = t.w;
     const double *nw = t.dx;
     double *tot = t.tot;
-    const auto total = [&](long long c, double v) { if (c * SCAN_CHUNK < N) tot[c] = v; };
+    const auto total = [&](int r, double v) { if (segs.len[r]) tot[c0 + r] = v; };
     const auto none = [](long long, double) {};
     if (w)
-        block_chains<0, float>(lds, N, c0, tiles, [&](long long i) { return w[i]; }, none, total, none);
+        block_chains<0, float>(lds, segs, [&](long long i) { return w[i]; }, none, total, none);
     else
-        block_chains<0, double>(lds, N, c0, tiles, [&](long long i) { return nw[i]; }, none, total, none);
+        block_chains<0, double>(lds, segs, [&](long long i) { return nw[i]; }, none, total, none);
 }
 
 // Chains over the deficits and the excesses (both halves of both tables), storing the running
@@ -480,8 +464,9 @@ __global__ void __launch_bounds__(256) k_chain_weights(Tables T)
 __global__ void __launch_bounds__(256) k_chain_dx(Tables T)
 {
     __shared__ double lds[CHAIN_LDS];
+    __shared__ ChainSegs segs;
     long long b;
-    const Table &t = table_of(T, b);
+    const GraphTable &t = T.of(b);
     const long long nL = t.lights();
     const long long cL = LH_CDIV(nL, SCAN_CHUNK), gL = LH_CDIV(cL, WAVE_CHUNKS);
     const bool heavy = b >= gL;
@@ -489,407 +474,30 @@ __global__ void __launch_bounds__(256) k_chain_dx(Tables T)
     const long long n = heavy ? t.N - nL : nL;
     if (c0 * SCAN_CHUNK >= n) return;
     double *x = t.dx + (heavy ? nL : 0), *tot = t.tot + (heavy ? cL : 0), *mxl = t.mxl + (heavy ? cL : 0);
-    block_chains<2, double>(lds, n, c0, chain_tiles(n - c0 * SCAN_CHUNK), [&](long long i) { return x[i]; },
-                            [&](long long i, double v) { x[i] = v; },
-                            [&](long long c, double v) { if (c * SCAN_CHUNK < n) tot[c] = v; },
-                            [&](long long c, double v) { if (c * SCAN_CHUNK < n) mxl[c] = v; });
-}
-
-// The levels above the chunks, one workgroup per scan: the canonical scan of the chunk totals (its
-// own chains as above, the totals of those, at most 2,048 for 2^31 items, by one thread), which
-// becomes each chunk's offset.  tot is left with the chains' values.
-constexpr int LEVEL_THREADS = 256, LEVEL_TOP = 2048;
-
-__device__ __forceinline__ void scan_levels(double *tot, double *off, long long nch, double *lds, double *top,
-                                            double *topinc)
-{
-    const long long n1 = LH_CDIV(nch, SCAN_CHUNK);
-    for (long long c0 = 0; c0 < n1; c0 += WAVE_CHUNKS)
-        block_chains<1, double>(lds, nch, c0, chain_tiles(nch - c0 * SCAN_CHUNK), [&](long long i) { return tot[i]; },
-                                [&](long long i, double v) { tot[i] = v; },
-                                [&](long long c, double v) { if (c < n1) top[c] = v; }, [](long long, double) {});
+    chunk_segs(segs, c0, n);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        // chunks of 1,024 again: at most two, the second offset by the first one's total
-        double base = 0.0;
-        for (long long lo = 0; lo < n1; lo += SCAN_CHUNK) {
-            OpNeumaier::State st = OpNeumaier::init();
-            double v = 0.0;
-            for (long long i = lo; i < n1 && i < lo + SCAN_CHUNK; ++i) {
-                v = OpNeumaier::step(st, top[i]);
-                topinc[i] = lo ? OpNeumaier::combine(base, v) : v;
-            }
-            base = v;
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) off[0] = 0.0;
-    // (eight loads at a time: the compiler keeps each behind the store before it otherwise)
-    for (long long i0 = threadIdx.x; i0 + 1 < nch; i0 += 8 * LEVEL_THREADS) {
-        double v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = i0 + k * LEVEL_THREADS + 1 < nch ? tot[i0 + k * LEVEL_THREADS] : 0.0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const long long i = i0 + k * LEVEL_THREADS, c = i / SCAN_CHUNK;
-            if (i + 1 < nch) off[i + 1] = c ? OpNeumaier::combine(topinc[c - 1], v[k]) : v[k];
-        }
-    }
-    __syncthreads();
+    block_chains<2, double>(lds, segs, [&](long long i) { return x[i]; }, [&](long long i, double v) { x[i] = v; },
+                            [&](int r, double v) { if (segs.len[r]) tot[c0 + r] = v; },
+                            [&](int r, double v) { if (segs.len[r]) mxl[c0 + r] = v; });
 }
 
-// Total weight of each table: off[last chunk] + that chunk's total.  Flags ST_ZERO_TOTAL, in the
-// status word and (with what was flagged there before) in the result block.
-__global__ void __launch_bounds__(LEVEL_THREADS) k_levels_weights(Tables T, unsigned int *status, unsigned long long *cnt)
-{
-    __shared__ double lds[CHAIN_LDS];
-    __shared__ double top[LEVEL_TOP], topinc[LEVEL_TOP];
-    const Table &t = T.t[blockIdx.x];
-    const long long nch = LH_CDIV(t.N, SCAN_CHUNK);
-    const double last = t.tot[nch - 1];  // before the totals become their chains
-    __syncthreads();
-    scan_levels(t.tot, t.off, nch, lds, top, topinc);
-    if (threadIdx.x == 0) {
-        const double W = nch > 1 ? OpNeumaier::combine(t.off[nch - 1], last) : last;
-        *t.W = W;
-        const unsigned bad = !(W > 0.0) || isinf(W) ? ST_ZERO_TOTAL : 0u;
-        if ((atomicOr(status, bad) | bad) & ST_ZERO_TOTAL) atomicOr(&cnt[CNT_STATUS], (unsigned long long)ST_ZERO_TOTAL);
-    }
-}
-
-// Offsets and prefix maxima of the four deficit and excess scans (workgroup: table, half).
-__global__ void __launch_bounds__(LEVEL_THREADS) k_levels_dx(Tables T)
-{
-    __shared__ double lds[CHAIN_LDS];
-    __shared__ double top[LEVEL_TOP], topinc[LEVEL_TOP];
-    const Table &t = T.t[blockIdx.x >> 1];
-    const bool heavy = (blockIdx.x & 1) != 0;
-    const long long nL = t.lights(), n = heavy ? t.N - nL : nL;
-    if (n == 0) return;
-    const long long c0 = heavy ? LH_CDIV(nL, SCAN_CHUNK) : 0, nch = LH_CDIV(n, SCAN_CHUNK);
-    double *off = t.off + c0, *before = t.before + c0, *end = t.mxl + c0;
-    scan_levels(t.tot + c0, off, nch, lds, top, topinc);
-    // prefix maximum of off[c] + (the chunk's own maximum): a consecutive quarter of the chunks
-    // per wavefront, 4 x 64 of them at a time
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const long long per = LH_CDIV(nch, LEVEL_THREADS) * 64;
-    const long long lo = wave * per, hi = lo + per < nch ? lo + per : nch;
-    const double none = -__builtin_huge_val();
-    auto four = [&](long long c, double(&v)[4]) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const long long i = c + k * 64 + lane;
-            v[k] = i < hi ? off[i] + end[i] : none;
-        }
-    };
-    double m = none, v[4];
-    for (long long c = lo; c < hi; c += 256) {
-        four(c, v);
-        m = __builtin_fmax(m, __builtin_fmax(__builtin_fmax(v[0], v[1]), __builtin_fmax(v[2], v[3])));
-    }
-    for (int d = 32; d >= 1; d >>= 1) m = __builtin_fmax(m, __shfl_xor(m, d));
-    if (lane == 0) top[wave] = m;
-    __syncthreads();
-    double run = none;
-    for (int w = 0; w < wave; ++w) run = __builtin_fmax(run, top[w]);
-    for (long long c = lo; c < hi; c += 256) {
-        four(c, v);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            double inc = v[k];
-            for (int d = 1; d < 64; d <<= 1) {
-                const double y = __shfl_up(inc, d);
-                if (lane >= d) inc = __builtin_fmax(inc, y);
-            }
-            double exc = __shfl_up(inc, 1);
-            if (lane == 0) exc = none;
-            const long long i = c + k * 64 + lane;
-            if (i < hi) {
-                before[i] = __builtin_fmax(run, exc);
-                end[i] = __builtin_fmax(run, inc);
-            }
-            run = __builtin_fmax(run, __shfl(inc, 63));
-        }
-    }
-}
-
-// Lights (q < 1) among 1,024 consecutive items, per wavefront.
-__global__ void __launch_bounds__(256) k_split_count(Tables T)
-{
-    long long b;
-    const Table &t = table_of(T, b);
-    const int lane = threadIdx.x & 63;
-    const long long part = b * 4 + (threadIdx.x >> 6), lo = part * SPLIT_ITEMS;
-    if (lo >= t.N) return;
-    const double W = *t.W;
-    int32_t cnt = 0;
-#pragma unroll 4
-    for (int r = 0; r < SPLIT_ITEMS / 64; ++r) {
-        const long long i = lo + r * 64 + lane;
-        cnt += __popcll(__ballot(i < t.N && t.q(i < t.N ? i : 0, W) < 1.0));
-    }
-    if (lane == 0) t.blk[part] = cnt;
-}
-
-// Exclusive prefix sums of the light counts, in place, with the total behind them; one workgroup
-// per table, a run of counts per thread.
-__global__ void __launch_bounds__(1024) k_split_scan(Tables T)
-{
-    __shared__ int32_t ws[16];
-    const Table &t = T.t[blockIdx.x];
-    const long long nt = LH_CDIV(t.N, SPLIT_ITEMS), per = LH_CDIV(nt, 1024);
-    const long long lo = threadIdx.x * per, hi = lo + per < nt ? lo + per : nt;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int32_t s = 0;
-#pragma unroll 8
-    for (long long i = lo; i < hi; ++i) s += t.blk[i];
-    int32_t inc = s;
-    for (int d = 1; d < 64; d <<= 1) {
-        const int32_t y = __shfl_up(inc, d);
-        if (lane >= d) inc += y;
-    }
-    if (lane == 63) ws[wave] = inc;
-    __syncthreads();
-    int32_t run = inc - s;
-    for (int v = 0; v < wave; ++v) run += ws[v];
-#pragma unroll 8
-    for (long long i = lo; i < hi; ++i) {
-        const int32_t c = t.blk[i];
-        t.blk[i] = run;
-        run += c;
-    }
-    if (threadIdx.x == 1023) t.blk[nt] = run;
-}
-
-// Split into lights (deficits 1 - q, prefix of dx) and heavies (excesses q - 1, suffix, and their
-// items), each in index order.  q is computed again from the weight: cheaper than a pass that
-// stores it.
-__global__ void __launch_bounds__(256) k_split(Tables T)
-{
-    long long b;
-    const Table &t = table_of(T, b);
-    const int lane = threadIdx.x & 63;
-    const long long part = b * 4 + (threadIdx.x >> 6), lo = part * SPLIT_ITEMS;
-    if (lo >= t.N) return;
-    const double W = *t.W;
-    const long long nL = t.lights();
-    long long a = t.blk[part];
-#pragma unroll 4
-    for (int r = 0; r < SPLIT_ITEMS / 64; ++r) {
-        const long long i = lo + r * 64 + lane;
-        const double q = i < t.N ? t.q(i, W) : 1.0;
-        const unsigned long long mask = __ballot(q < 1.0);
-        const long long before = a + __popcll(mask & ((1ull << lane) - 1ull));  // lights before item i
-        if (i < t.N) {
-            if (q < 1.0) {
-                t.dx[before] = __dsub_rn(1.0, q);
-            } else {
-                t.dx[nL + (i - before)] = __dsub_rn(q, 1.0);
-                t.idx[i - before] = (int32_t)i;
-            }
-        }
-        a += __popcll(mask);
-    }
-}
-
-// First position in [lo, hi) whose value is not `below` (values are monotone), by a whole
-// wavefront: 64 probes at a time.
-template <class Below>
-__device__ __forceinline__ long long wave_search(long long lo, long long hi, Below below)
-{
-    const int lane = threadIdx.x & 63;
-    while (lo < hi) {
-        const long long step = LH_CDIV(hi - lo, 64);
-        const long long pos = lo + (lane + 1) * step - 1;  // last position of this lane's part
-        const long long parts = __popcll(__ballot(pos < hi && below(pos)));
-        lo += parts * step;
-        if (step == 1) break;
-        if (lo + step - 1 < hi) hi = lo + step - 1;  // its part's last position is not below
-    }
-    return lo;
-}
-
-// The same over a scan: first among the chunks' last values, then inside the chunk.
-template <class Less>
-__device__ __forceinline__ long long wave_search_scan(const Scan &x, long long n, Less less)
-{
-    // n <= x.n positions; the chunk's `end` stands for its last position, which may lie past n
-    const long long nch = LH_CDIV(n, SCAN_CHUNK);
-    const long long c = wave_search(0, nch, [&](long long k) { return less(x.end[k]); });
-    if (c >= nch) return n;
-    const long long lo = c * SCAN_CHUNK, hi = lo + SCAN_CHUNK < n ? lo + SCAN_CHUNK : n;
-    const double before = x.before[c], off = x.off[c];
-    return wave_search(lo, hi, [&](long long i) { return less(__builtin_fmax(before, off + x.loc[i])); });
-}
-
-// Records: light a with start S_a = D[a-1] (S_0 = 0) aliases heavy #{X[k] <= S_a}; heavy k finds
-// the last light that starts before X[k].  A workgroup writes 1,024 consecutive items, whose
-// lights and whose heavies are each a consecutive run: whole lines are written, and the item's
-// own weight and endpoints are read in order.  Both sequences are monotone, so the answers of a
-// run lie between those of its two ends, which one wavefront each searches for; the stretch of
-// the other sequence between them is staged in LDS when it fits (it is about as long as the run
-// times the ratio of the halves), and the items' own searches touch no memory.  C2's 16.8 M arcs:
-// 0.51 ms for both tables, 0.87 ms with a thread per light and per heavy that searched all of the
-// other half and wrote every second record of a line.  What is left is 0.24 ms of traffic at a
-// copy's rate and 0.14 ms of heat bytes (67 M scattered reads).
-constexpr int REC_ITEMS = 1024, REC_STAGE = 1024;
-static_assert(REC_ITEMS == SPLIT_ITEMS, "a workgroup's first light is its split count");
-
-// The two halves' scans lie one behind the other: position p of half `heavy` is element
-// (heavy ? nL : 0) + p, in chunk (heavy ? cL : 0) + p / 1024.
 __global__ void __launch_bounds__(256) k_records(Tables T)
 {
-    __shared__ double sx[REC_STAGE], sd[REC_STAGE + 1];
-    __shared__ long long ends[4];
-    __shared__ int32_t wc[4];
+    __shared__ RecLds lds;
     long long b;
-    const Table &t = table_of(T, b);
-    const long long N = t.N, nL = t.lights(), nH = N - nL, cL = LH_CDIV(nL, SCAN_CHUNK), i0 = b * REC_ITEMS;
-    const long long i1 = i0 + REC_ITEMS < N ? i0 + REC_ITEMS : N;
-    const long long a0 = t.blk[b], a1 = t.blk[b + 1], h0 = i0 - a0, h1 = i1 - a1;  // the runs
-    const Scan D = t.half(false, nL), X = t.half(true, nL);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const double W = *t.W;
-    // lights: count of X <= S_a; heavies: count of D < X[k] over the lights but the last (the
-    // start of light a >= 1 is D[a - 1])
-    const long long nD = nL > 0 ? nL - 1 : 0;
-    {
-        long long k = 0;
-        if (wave < 2) {
-            const long long a = wave == 0 ? a0 : a1 - 1;
-            if (a1 > a0 && nH > 0) {
-                const double s = a == 0 ? 0.0 : D.at(a - 1);
-                k = wave_search_scan(X, nH, [&](double v) { return v <= s; });
-            }
-        } else {
-            const long long p = wave == 2 ? h0 : h1 - 1;
-            if (h1 > h0 && nD > 0) {
-                const double x = X.at(p);
-                k = wave_search_scan(D, nD, [&](double v) { return v < x; });
-            }
-        }
-        if (lane == 0) ends[wave] = k;
-    }
-    // item r of this thread: i0 + wave * 256 + r * 64 + lane.  Each step below is taken for all
-    // four items before the next, so that their loads are in flight together.
-    const long long first = i0 + wave * 256 + lane;
-    double q[4];
-    unsigned long long mask[4];
-    int32_t cnt = 0;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const long long i = first + r * 64;
-        const double qi = t.q(i < i1 ? i : i1 - 1, W);
-        q[r] = i < i1 ? qi : 1.0;
-        mask[r] = __ballot(q[r] < 1.0);
-        cnt += __popcll(mask[r]);
-    }
-    if (lane == 0) wc[wave] = cnt;
-    __syncthreads();
-    const long long x0 = ends[0], d0 = ends[2];
-    const int xn = (int)(ends[1] - x0), dn = (int)(ends[3] - d0), dr = dn + (nL > 0 ? 1 : 0);
-    const bool staged = xn <= REC_STAGE && dr <= REC_STAGE + 1;
-    if (staged) {
-        for (int i = threadIdx.x; i < xn; i += 256) sx[i] = X.at(x0 + i);
-        for (int i = threadIdx.x; i < dr; i += 256) sd[i] = D.at(d0 + i);  // heavies read D at their answer too
-    }
-    long long a = a0;
-    for (int v = 0; v < wave; ++v) a += wc[v];
-    long long pos[4];  // lights before the item, or its place among the heavies
-    double key[4];     // S_a, or X[k]
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const long long i = first + r * 64;
-        const long long before = a + __popcll(mask[r] & ((1ull << lane) - 1ull));
-        a += __popcll(mask[r]);
-        const bool light = q[r] < 1.0;
-        pos[r] = light ? before : (i < i1 ? i - before : 0);
-        const long long p = light ? (before > 0 ? before - 1 : 0) : pos[r];
-        const long long c = (light ? 0 : cL) + p / SCAN_CHUNK;
-        const double v = nH == 0 && !light ? 0.0 : __builtin_fmax(t.before[c], t.off[c] + t.dx[(light ? 0 : nL) + p]);
-        key[r] = light && before == 0 ? 0.0 : v;
-    }
-    __syncthreads();
-    int lo[4] = {0, 0, 0, 0};
-    if (staged) {
-        int hi[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) hi[r] = q[r] < 1.0 ? xn : dn;
-        for (int left = xn > dn ? xn : dn; left > 0; left >>= 1) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const bool light = q[r] < 1.0;
-                const int mid = (lo[r] + hi[r]) >> 1;
-                const double y = light ? sx[mid < xn ? mid : 0] : sd[mid];
-                const bool up = lo[r] < hi[r] && (light ? y <= key[r] : y < key[r]);
-                if (up) lo[r] = mid + 1;
-                else if (lo[r] < hi[r]) hi[r] = mid;
-            }
-        }
-    } else {
-#pragma unroll 1
-        for (int r = 0; r < 4; ++r) {
-            const bool light = q[r] < 1.0;
-            int l = 0, h = light ? xn : dn;
-            while (l < h) {
-                const int mid = l + ((h - l) >> 1);
-                const double y = light ? X.at(x0 + mid) : D.at(d0 + mid);
-                if (light ? y <= key[r] : y < key[r]) l = mid + 1;
-                else h = mid;
-            }
-            lo[r] = l;
-        }
-    }
-    unsigned long long thr[4];
-    int32_t al[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const bool light = q[r] < 1.0;
-        long long k = -1;  // the heavy that the item aliases (-1: itself)
-        thr[r] = ~0ull;
-        if (light) {
-            if (nH > 0) {
-                k = x0 + lo[r] < nH - 1 ? x0 + lo[r] : nH - 1;
-                thr[r] = prob_to_thr(q[r]);
-            }
-        } else if (pos[r] < nH - 1 && nL > 0 && 0.0 < key[r]) {
-            // light d0 + lo is the last that starts before X[k]; its deficit sum past X[k] is
-            // what overflows to the next heavy
-            double ov = __dsub_rn(staged ? sd[lo[r]] : D.at(d0 + lo[r]), key[r]);
-            if (ov < 0.0) ov = 0.0;
-            if (ov > 0.0) {
-                const double pr = __dsub_rn(1.0, ov);
-                thr[r] = prob_to_thr(pr < 0.0 ? 0.0 : pr);
-                k = pos[r] + 1;
-            }
-        }
-        const int32_t item = t.idx[k < 0 ? 0 : k];
-        al[r] = k < 0 ? (int32_t)(first + r * 64) : item;
-    }
-    if (t.out.erec) {
-        int32_t e[4][4];  // endpoints: source and destination, of the item and of its alias
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const long long i = first + r * 64 < i1 ? first + r * 64 : i1 - 1;
-            const long long z = first + r * 64 < i1 ? al[r] : i1 - 1;
-            e[r][0] = t.out.src[i];
-            e[r][1] = t.out.dst[i];
-            e[r][2] = t.out.src[z];
-            e[r][3] = t.out.dst[z];
-        }
-        uint32_t heat[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            heat[r] = (uint32_t)t.out.heat[e[r][0]] | ((uint32_t)t.out.heat[e[r][1]] << 8) |
-                      ((uint32_t)t.out.heat[e[r][2]] << 16) | ((uint32_t)t.out.heat[e[r][3]] << 24);
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (first + r * 64 < i1)
-                t.out.erec[first + r * 64] = EdgeRec{thr[r], al[r], e[r][0], e[r][1], e[r][2], e[r][3], heat[r]};
-    } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (first + r * 64 < i1) write_rec(t.out, first + r * 64, thr[r], al[r]);
+    const GraphTable &t = T.of(b);
+    records_run<4>(t, b, lds);
+}
+
+// Total weights.  Flags ST_ZERO_TOTAL, in the status word and (with what was flagged there before)
+// in the result block.
+__global__ void __launch_bounds__(LEVEL_THREADS) k_levels_weights(Tables T, unsigned int *status, unsigned long long *cnt)
+{
+    __shared__ LevelLds l;
+    const double W = levels_weight(T.t[blockIdx.x], l);
+    if (threadIdx.x == 0) {
+        const unsigned bad = !(W > 0.0) || isinf(W) ? ST_ZERO_TOTAL : 0u;
+        if ((atomicOr(status, bad) | bad) & ST_ZERO_TOTAL) atomicOr(&cnt[CNT_STATUS], (unsigned long long)ST_ZERO_TOTAL);
     }
 }
 
@@ -925,13 +533,13 @@ lh_status build_alias(lh_handle *h, void *scratch, size_t bytes)
     uint8_t *heat = (uint8_t *)(h->ws + h->lay.nheat);
     Tables T;
     for (int k = 0; k < 2; ++k) {
-        Table &t = T.t[k];
+        GraphTable &t = T.t[k];
         t.N = k == 0 ? h->n : h->m;
         t.w = k == 0 ? nullptr : h->w;
         t.deg = deg;
         t.dx = (double *)(sc + L.dx[k]);
-        t.idx = (int32_t *)(sc + L.idx[k]);
-        t.blk = (int32_t *)(sc + L.blk[k]);
+        t.idx = (uint32_t *)(sc + L.idx[k]);
+        t.blk = (uint32_t *)(sc + L.blk[k]);
         t.tot = (double *)(sc + L.tot[k]);
         t.mxl = (double *)(sc + L.mxl[k]);
         t.off = (double *)(sc + L.off[k]);
@@ -953,12 +561,12 @@ lh_status build_alias(lh_handle *h, void *scratch, size_t bytes)
                        cnt);
     // Lights and heavies, their scans, the records.
     g = spread(T, 4 * SPLIT_ITEMS);
-    hipLaunchKernelGGL(k_split_count, dim3(g), blk, 0, s, T);
-    hipLaunchKernelGGL(k_split_scan, dim3(2), dim3(1024), 0, s, T);
-    hipLaunchKernelGGL(k_split, dim3(g), blk, 0, s, T);
+    hipLaunchKernelGGL(k_split_count<Tables>, dim3(g), blk, 0, s, T);
+    hipLaunchKernelGGL(k_split_scan<Tables>, dim3(2), dim3(1024), 0, s, T);
+    hipLaunchKernelGGL(k_split<Tables>, dim3(g), blk, 0, s, T);
     g = spread_halves(T, (long long)WAVE_CHUNKS * SCAN_CHUNK);
     hipLaunchKernelGGL(k_chain_dx, dim3(g), blk, 0, s, T);
-    hipLaunchKernelGGL(k_levels_dx, dim3(4), blk, 0, s, T);
+    hipLaunchKernelGGL(k_levels_dx<Tables>, dim3(4), blk, 0, s, T);
     g = spread(T, REC_ITEMS);
     hipLaunchKernelGGL(k_records, dim3(g), blk, 0, s, T);
     unsigned long long host[CNT_WORDS];

@@ -1,12 +1,17 @@
-// Canonical chunked inclusive scan on the GPU.
+// Canonical chunked scans of binary64 values on the GPU.
 //
-// The association order is fixed: chunk c covers [c*1024, min((c+1)*1024, n)); one
-// thread runs the chunk's left-to-right chain; the chunk totals are scanned the same
-// way, recursively; element i of chunk c > 0 becomes combine(inc[c-1], loc[i]).  For
-// the binary64 compensated sum this order is part of the definition of the alias
-// tables' normalisation and prefix sums, so the GPU result is bitwise reproducible
-// against any implementation of the same definition.  For max and for integer sums
-// the order does not matter, and the same code is reused.
+// The association order is fixed: chunk c covers [c*1024, min((c+1)*1024, n)); the chunk's values
+// are one left-to-right chain; the chunk totals are scanned the same way, recursively; element i
+// of chunk c > 0 becomes combine(inc[c-1], loc[i]).  For the binary64 compensated sum this order is
+// part of the definition of the alias tables' normalisation and prefix sums, so the GPU result is
+// bitwise reproducible against any implementation of the same definition.
+//
+// The constructions read their prefix sums only through searches, so no scan is ever written out
+// element by element with its offsets: a scan is the chains' values within each chunk and, per
+// chunk, the offset of the chunk (the canonical scan of the totals before it).  They use its
+// running maximum; rounding is monotone, so the running maximum of off + x within a chunk is
+// off + (the running maximum of x), and across chunks it is enough to keep the largest value
+// before the chunk:  value(i) = max(before[c], off[c] + loc[i]),  c = i / 1024.
 //
 // This header is compiled only into translation units built with -ffp-contract=off.
 #pragma once
@@ -19,7 +24,6 @@ constexpr int SCAN_CHUNK = 1024;
 
 // Neumaier-compensated running sum; the chunk value is s + comp after each element.
 struct OpNeumaier {
-    using T = double;
     struct State {
         double s, c;
     };
@@ -37,37 +41,8 @@ struct OpNeumaier {
     __device__ static double combine(double off, double loc) { return off + loc; }
 };
 
-struct OpMax {
-    using T = double;
-    struct State {
-        double m;
-    };
-    __device__ static State init() { return State{-__builtin_huge_val()}; }
-    __device__ static double step(State &st, double x)
-    {
-        st.m = x > st.m ? x : st.m;
-        return st.m;
-    }
-    __device__ static double combine(double off, double loc) { return loc > off ? loc : off; }
-};
-
-template <class I>
-struct OpAdd {
-    using T = I;
-    struct State {
-        I s;
-    };
-    __device__ static State init() { return State{I(0)}; }
-    __device__ static I step(State &st, I x)
-    {
-        st.s += x;
-        return st.s;
-    }
-    __device__ static I combine(I off, I loc) { return off + loc; }
-};
-
 // ---------------------------------------------------------------------------
-// The chains of up to 16 consecutive chunks of one array of non-negative binary64 values, by one
+// The chains of up to 16 chunks of non-negative binary64 values, anywhere in one array, by one
 // workgroup of 256 threads.
 //
 // Written out, a Neumaier step is nine dependent operations, and one thread per chunk waits
@@ -82,55 +57,77 @@ struct OpAdd {
 //   wavefronts 2, 3  move tile t + 1 from registers to LDS and load tile t + 5
 //   all           e of tile t, s + c of tile t - 1, results of tile t - 2 to memory
 // A tile takes 0.9 us, so a scan's chains take 30 us whatever its length up to 16.8 M elements
-// (C2's two weight scans together 55 us, its four deficit and excess scans 92 us).
-// (roles rotate with the workgroup's number, so that the chains of several resident ones do not
-// share a SIMD).  16 chunks, not 64, spread small arrays over more compute units.
+// (16.8 M arcs and 1.05 M nodes: the two weight scans together 55 us, the four deficit and excess
+// scans 92 us).  Roles rotate with the workgroup's number, so that the chains of several resident
+// ones do not share a SIMD.  16 chunks, not 64, spread small arrays over more compute units.
 //
-// Elements past the end read as 0, which changes neither s, c nor the maximum.
+// Elements past a chunk's end read as 0, which changes neither s, c nor the maximum.
 // WHAT: 0 only the chunk totals, 1 store s + c after each element, 2 store its running maximum.
-// tiles: 32-element tiles per chunk to run (uniform).  total(c, s + c) is called for every chunk
-// of the 16, maximum(c, m) too for WHAT 2; chunks past the end included.  load(i) only fetches
-// (any index it is given is in range) and the value becomes binary64 a tile later, so that
-// nothing waits for a load in flight; n >= 1.
+// segs: the chunks (in LDS, visible to the workgroup; length 0: none).  total(r, s + c) is called
+// for every r < 16, maximum(r, m) too for WHAT 2.  load(i) only fetches (any index it is given is
+// in range) and the value becomes binary64 a tile later, so that nothing waits for a load in flight.
 constexpr int WAVE_CHUNKS = 16;
 constexpr int CHAIN_TILE = 32;
 constexpr int CHAIN_ROW = CHAIN_TILE + 1;
 constexpr int CHAIN_BUF = WAVE_CHUNKS * CHAIN_ROW;
 constexpr int CHAIN_LDS = 6 * CHAIN_BUF + WAVE_CHUNKS;  // doubles per workgroup
 
-static inline __host__ __device__ int chain_tiles(long long rest)
+struct ChainSegs {
+    long long start[WAVE_CHUNKS];
+    int len[WAVE_CHUNKS];  // at most SCAN_CHUNK
+};
+
+// Chunks c0 .. c0 + 15 of an array of n elements (threads below 16; no barrier here).
+__device__ __forceinline__ void chunk_segs(ChainSegs &sg, long long c0, long long n)
 {
-    return rest >= SCAN_CHUNK ? SCAN_CHUNK / CHAIN_TILE : (int)LH_CDIV(rest, CHAIN_TILE);
+    if (threadIdx.x >= WAVE_CHUNKS) return;
+    const long long lo = (c0 + threadIdx.x) * SCAN_CHUNK, left = n - lo;
+    sg.start[threadIdx.x] = lo;
+    sg.len[threadIdx.x] = left <= 0 ? 0 : left < SCAN_CHUNK ? (int)left : SCAN_CHUNK;
 }
 
 template <int WHAT, class Raw, class Load, class Store, class Total, class Maximum>
-__device__ __forceinline__ void block_chains(double *lds, long long n, long long c0, int tiles, Load load, Store store,
-                                             Total total, Maximum maximum)
+__device__ __forceinline__ void block_chains(double *lds, const ChainSegs &segs, Load load, Store store, Total total,
+                                             Maximum maximum)
 {
     double *const X = lds, *const S = lds + 2 * CHAIN_BUF, *const E = lds + 4 * CHAIN_BUF, *const O = lds + 5 * CHAIN_BUF,
                   *const carry = lds + 6 * CHAIN_BUF;
     const int lane = threadIdx.x & 63, role = ((threadIdx.x >> 6) + blockIdx.x) & 3;
-    // the loaders' elements of a tile: four each
-    const int l0 = (role & 1) * 64 + lane;
+    int most = 0;
+#pragma unroll
+    for (int k = 0; k < WAVE_CHUNKS; ++k) most = segs.len[k] > most ? segs.len[k] : most;
+    const int tiles = LH_CDIV(most, CHAIN_TILE);
+    // the loaders' elements of a tile: four each, in chunks (l0 >> 5) + 4 q
+    const int l0 = (role & 1) * 64 + lane, lcol = l0 & 31;
     Raw r[4][4];
-    auto at = [&](int t, int q) {
-        const int e = l0 + q * 128;
-        return (c0 + (e >> 5)) * SCAN_CHUNK + t * CHAIN_TILE + (e & 31);
-    };
+    long long lstart[4];
+    int llen[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        lstart[q] = segs.start[(l0 >> 5) + 4 * q];
+        llen[q] = segs.len[(l0 >> 5) + 4 * q];
+    }
     auto fetch = [&](int t, Raw(&d)[4]) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const long long i = at(t, q);
-            d[q] = load(i < n ? i : n - 1);
+            const int k = t * CHAIN_TILE + lcol;
+            d[q] = load(llen[q] > 0 ? lstart[q] + (k < llen[q] ? k : llen[q] - 1) : segs.start[0]);
         }
     };
     auto place = [&](int t, const Raw(&d)[4]) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = l0 + q * 128;
-            X[(t & 1) * CHAIN_BUF + (e >> 5) * CHAIN_ROW + (e & 31)] = at(t, q) < n ? (double)d[q] : 0.0;
-        }
+        for (int q = 0; q < 4; ++q)
+            X[(t & 1) * CHAIN_BUF + ((l0 >> 5) + 4 * q) * CHAIN_ROW + lcol] =
+                t * CHAIN_TILE + lcol < llen[q] ? (double)d[q] : 0.0;
     };
+    // the elements of a tile whose errors, sums and stores this thread takes: two
+    long long estart[2];
+    int elen[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        estart[q] = segs.start[((int)threadIdx.x + q * 256) >> 5];
+        elen[q] = segs.len[((int)threadIdx.x + q * 256) >> 5];
+    }
     if (role >= 2) {
 #pragma unroll
         for (int p = 0; p < 4; ++p) fetch(p, r[p]);
@@ -187,12 +184,12 @@ __device__ __forceinline__ void block_chains(double *lds, long long n, long long
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const int e = (int)threadIdx.x + q * 256, col = e & 31, a = (e >> 5) * CHAIN_ROW + col;
-                const long long i = (c0 + (e >> 5)) * SCAN_CHUNK + it * CHAIN_TILE + col;
-                if (third && i - 2 * CHAIN_TILE < n) store(i - 2 * CHAIN_TILE, O[a]);
+                const int i = it * CHAIN_TILE + col;
+                if (third && i - 2 * CHAIN_TILE < elen[q]) store(estart[q] + (i - 2 * CHAIN_TILE), O[a]);
                 if (WHAT != 0 && prev) {
                     const double v = S[last + a] + E[a];
                     if (WHAT == 2) O[a] = v;
-                    else if (i - CHAIN_TILE < n) store(i - CHAIN_TILE, v);
+                    else if (i - CHAIN_TILE < elen[q]) store(estart[q] + (i - CHAIN_TILE), v);
                 }
                 if (cur) {
                     const double s = S[buf + a], p = col ? S[buf + a - 1] : carry[e >> 5], b = s - p;
@@ -204,88 +201,124 @@ __device__ __forceinline__ void block_chains(double *lds, long long n, long long
     }
     if (role == 0) {
         const double c = __shfl(acc, (lane & (WAVE_CHUNKS - 1)) + WAVE_CHUNKS);
-        if (lane < WAVE_CHUNKS) total(c0 + lane, acc + c);
+        if (lane < WAVE_CHUNKS) total(lane, acc + c);
     }
-    if (WHAT == 2 && role == 1 && lane < WAVE_CHUNKS) maximum(c0 + lane, mx);
+    if (WHAT == 2 && role == 1 && lane < WAVE_CHUNKS) maximum(lane, mx);
 }
 
-// Elements a chain loads ahead of its arithmetic: the chain itself is one dependent
-// sequence, but its loads are not, so they are issued in blocks of this many.
-constexpr int CHAIN_BLOCK = 64;
+struct Scan {
+    const double *loc;     // [n] per element, within its chunk
+    const double *off;     // [chunks] canonical scan of the totals before the chunk (0 for the first)
+    const double *before;  // [chunks] largest value before the chunk (-inf for the first)
+    const double *end;     // [chunks] value of the chunk's last element
+    long long n;
 
-// The left-to-right chain of one chunk [lo, hi), in place or not (each block is loaded
-// before any of its results is stored).
-template <class Op>
-__device__ __forceinline__ typename Op::T chain(const typename Op::T *x, typename Op::T *out, long long lo,
-                                                long long hi)
+    __device__ __forceinline__ double at(long long i) const
+    {
+        const long long c = i / SCAN_CHUNK;
+        return __builtin_fmax(before[c], off[c] + loc[i]);
+    }
+};
+
+// The levels above the chunks, one workgroup per scan: the canonical scan of the chunk totals (its
+// own chains as above, the totals of those, at most 4,096 for 2^32 items, by one thread), which
+// becomes each chunk's offset.  tot is left with the chains' values.
+constexpr int LEVEL_THREADS = 256, LEVEL_TOP = 4096;
+
+struct LevelLds {
+    double chains[CHAIN_LDS];
+    double top[LEVEL_TOP];
+    ChainSegs segs;
+};
+
+__device__ __forceinline__ void scan_levels(double *tot, double *off, long long nch, LevelLds &l)
 {
-    typename Op::State st = Op::init();
-    typename Op::T last{};
-    long long i = lo;
-    for (; i + CHAIN_BLOCK <= hi; i += CHAIN_BLOCK) {
-        typename Op::T v[CHAIN_BLOCK];
-#pragma unroll
-        for (int k = 0; k < CHAIN_BLOCK; ++k) v[k] = x[i + k];
-#pragma unroll
-        for (int k = 0; k < CHAIN_BLOCK; ++k) {
-            last = Op::step(st, v[k]);
-            out[i + k] = last;
+    double *const top = l.top;
+    const long long n1 = LH_CDIV(nch, SCAN_CHUNK);
+    for (long long c0 = 0; c0 < n1; c0 += WAVE_CHUNKS) {
+        chunk_segs(l.segs, c0, nch);
+        __syncthreads();
+        block_chains<1, double>(l.chains, l.segs, [&](long long i) { return tot[i]; },
+                                [&](long long i, double v) { tot[i] = v; },
+                                [&](int r, double v) { if (c0 + r < n1) top[c0 + r] = v; }, [](int, double) {});
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        // chunks of 1,024 again: at most four, offset by the totals before them (the totals of
+        // their totals are one chunk)
+        OpNeumaier::State up = OpNeumaier::init();
+        double base = 0.0;
+        for (long long lo = 0; lo < n1; lo += SCAN_CHUNK) {
+            OpNeumaier::State st = OpNeumaier::init();
+            double v = 0.0;
+            for (long long i = lo; i < n1 && i < lo + SCAN_CHUNK; ++i) {
+                v = OpNeumaier::step(st, top[i]);
+                top[i] = lo ? OpNeumaier::combine(base, v) : v;
+            }
+            base = OpNeumaier::step(up, v);
         }
     }
-    for (; i < hi; ++i) {
-        last = Op::step(st, x[i]);
-        out[i] = last;
+    __syncthreads();
+    if (threadIdx.x == 0) off[0] = 0.0;
+    // (eight loads at a time: the compiler keeps each behind the store before it otherwise)
+    for (long long i0 = threadIdx.x; i0 + 1 < nch; i0 += 8 * LEVEL_THREADS) {
+        double v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = i0 + k * LEVEL_THREADS + 1 < nch ? tot[i0 + k * LEVEL_THREADS] : 0.0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const long long i = i0 + k * LEVEL_THREADS, c = i / SCAN_CHUNK;
+            if (i + 1 < nch) off[i + 1] = c ? OpNeumaier::combine(top[c - 1], v[k]) : v[k];
+        }
     }
-    return last;
+    __syncthreads();
 }
 
-template <class Op>
-__global__ void __launch_bounds__(256) k_chunk_chain(const typename Op::T *x, typename Op::T *out,
-                                                     long long n, typename Op::T *tot)
+// Prefix maxima of a scan's chunks: end[c] (the chunk's own maximum) becomes the largest value up to
+// the chunk's last element, before[c] the largest before the chunk.
+__device__ __forceinline__ void scan_maxima(const double *off, double *before, double *end, long long nch, LevelLds &l)
 {
-    long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    long long nch = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
-    if (c >= nch) return;
-    long long lo = c * SCAN_CHUNK, hi = lo + SCAN_CHUNK < n ? lo + SCAN_CHUNK : n;
-    tot[c] = chain<Op>(x, out, lo, hi);
-}
-
-template <class Op>
-__global__ void __launch_bounds__(256) k_chunk_offset(typename Op::T *out, long long n,
-                                                      const typename Op::T *inc)
-{
-    long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    long long c = i / SCAN_CHUNK;
-    if (c == 0) return;
-    out[i] = Op::combine(inc[c - 1], out[i]);
-}
-
-// Elements of level storage needed for a scan of n items.
-static inline long long scan_levels_size(long long n)
-{
-    long long total = 0;
-    while (n > 1) {
-        n = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
-        total += n;
+    double *const top = l.top;
+    // a consecutive quarter of the chunks per wavefront, 4 x 64 of them at a time
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const long long per = LH_CDIV(nch, LEVEL_THREADS) * 64;
+    const long long lo = wave * per, hi = lo + per < nch ? lo + per : nch;
+    const double none = -__builtin_huge_val();
+    auto four = [&](long long c, double(&v)[4]) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const long long i = c + k * 64 + lane;
+            v[k] = i < hi ? off[i] + end[i] : none;
+        }
+    };
+    double m = none, v[4];
+    for (long long c = lo; c < hi; c += 256) {
+        four(c, v);
+        m = __builtin_fmax(m, __builtin_fmax(__builtin_fmax(v[0], v[1]), __builtin_fmax(v[2], v[3])));
     }
-    return total + 8;
-}
-
-// Inclusive scan of x[0..n) into out (out may equal x).  levels must hold
-// scan_levels_size(n) elements.
-template <class Op>
-static void chunk_scan(const typename Op::T *x, typename Op::T *out, long long n,
-                       typename Op::T *levels, hipStream_t s)
-{
-    if (n <= 0) return;
-    long long nch = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
-    hipLaunchKernelGGL(k_chunk_chain<Op>, dim3((unsigned)LH_CDIV(nch, 256)), dim3(256), 0, s, x, out,
-                       n, levels);
-    if (nch > 1) {
-        chunk_scan<Op>(levels, levels, nch, levels + nch, s);
-        hipLaunchKernelGGL(k_chunk_offset<Op>, dim3((unsigned)LH_CDIV(n, 256)), dim3(256), 0, s, out,
-                           n, levels);
+    for (int d = 32; d >= 1; d >>= 1) m = __builtin_fmax(m, __shfl_xor(m, d));
+    if (lane == 0) top[wave] = m;
+    __syncthreads();
+    double run = none;
+    for (int w = 0; w < wave; ++w) run = __builtin_fmax(run, top[w]);
+    for (long long c = lo; c < hi; c += 256) {
+        four(c, v);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            double inc = v[k];
+            for (int d = 1; d < 64; d <<= 1) {
+                const double y = __shfl_up(inc, d);
+                if (lane >= d) inc = __builtin_fmax(inc, y);
+            }
+            double exc = __shfl_up(inc, 1);
+            if (lane == 0) exc = none;
+            const long long i = c + k * 64 + lane;
+            if (i < hi) {
+                before[i] = __builtin_fmax(run, exc);
+                end[i] = __builtin_fmax(run, inc);
+            }
+            run = __builtin_fmax(run, __shfl(inc, 63));
+        }
     }
 }
 

@@ -7,9 +7,8 @@
 // src[e], head dst[e]), entry m + e arc e backwards; both weigh w[e].  Row x (the
 // neighbourhood N(x)) lists the entries with tail x in increasing entry index: a stable
 // radix sort of the entries by tail.  discrete(N(x)) is the alias table of the row's
-// weights, built exactly as the edge and negative tables are (alias.hip) but per row:
-// the canonical scans restart at every row (segscan.hpp), and items are numbered within
-// the row.
+// weights, built exactly as the edge and negative tables are (table.hpp) but per row:
+// the canonical scans restart at every row, and items are numbered within the row.
 //
 // Walk k: Philox4x64-10 key (seed, 5 * 2^32 | graph_id).  Block (k, 0, 0, 0) draws the
 // root arc from the edge table (Algorithm 3's weight-normalised edge distribution):
@@ -23,9 +22,8 @@
 #include <cmath>
 
 #include "handle.hpp"
-#include "scan.hpp"
-#include "segscan.hpp"
 #include "sort.hpp"
+#include "table.hpp"
 #include "tile.hpp"
 
 #pragma clang fp contract(off)
@@ -63,32 +61,43 @@ WalkLayout walk_layout(long long n, long long m, int L, int W, long long Bw)
 
 namespace {
 
+// A row longer than ROW_SHORT, as a table of its own (table.hpp).
+constexpr int ROW_SHORT = 256, ROW_HUGE = 64 * SCAN_CHUNK;
+
+struct LongRow {
+    long long lo, len;  // its entries
+    long long slot;     // its first word in the arrays of chunk values: len / 1024 + 2 of them at most
+    double W;
+};
+
 struct WalkScratch {
-    size_t k0, w0, h0, k1, w1, h1, s0, q, hist, part, sstart, slen, arena, total;
-    long long E;
-    size_t arena_bytes;
+    size_t k0, w0, h0, k1, w1, h1, hist, part, cnt, rows, huge, slot_row, blk, tot, mxl, off, before, total;
 };
 
 WalkScratch walk_scratch_layout(long long n, long long m)
 {
+    (void)n;
     WalkScratch L;
     const long long E = 2 * m > 0 ? 2 * m : 1;
-    L.E = E;
+    const long long rows = E / (ROW_SHORT + 1) + 1, slots = E / SCAN_CHUNK + 2 * rows;
     size_t off = 0;
-    L.k0 = carve(off, 4 * (size_t)(E + 1));
+    L.k0 = carve(off, 4 * (size_t)E);
     L.w0 = carve(off, 4 * (size_t)E);
     L.h0 = carve(off, 4 * (size_t)E);
-    L.k1 = carve(off, 4 * (size_t)(E + 1));
+    L.k1 = carve(off, 4 * (size_t)E);
     L.w1 = carve(off, 4 * (size_t)E);
     L.h1 = carve(off, 4 * (size_t)E);
-    L.s0 = carve(off, 8 * (size_t)E);
-    L.q = carve(off, 8 * (size_t)E);
     L.hist = carve(off, 4 * (size_t)sort_hist_size(E));
-    L.part = carve(off, 4 * (size_t)std::max(sort_part_size(E), LH_CDIV(E + 1, (long long)SORT_TILE) + 1));
-    L.sstart = carve(off, 8 * (size_t)(2 * n));
-    L.slen = carve(off, 8 * (size_t)(2 * n));
-    L.arena_bytes = std::max(seg_scan_bytes(n, E), seg_scan_bytes(2 * n, E));
-    L.arena = carve(off, L.arena_bytes);
+    L.part = carve(off, 4 * (size_t)sort_part_size(E));
+    L.cnt = carve(off, 3 * sizeof(unsigned long long));
+    L.rows = carve(off, sizeof(LongRow) * (size_t)rows);
+    L.huge = carve(off, 4 * (size_t)(E / ROW_HUGE + 1));
+    L.slot_row = carve(off, 4 * (size_t)slots);
+    L.blk = carve(off, 4 * (size_t)slots);
+    L.tot = carve(off, 8 * (size_t)slots);
+    L.mxl = carve(off, 8 * (size_t)slots);
+    L.off = carve(off, 8 * (size_t)slots);
+    L.before = carve(off, 8 * (size_t)slots);
     L.total = off;
     return L;
 }
@@ -110,169 +119,491 @@ struct WalkEntries {
     }
 };
 
-// Items of a 0/1 array before position i, from k_sort_scan's parts.
-struct Counts {
-    const uint32_t *x, *part;
-    __device__ __forceinline__ long long before(long long i) const { return (long long)(x[i] + part[i / SORT_TILE]); }
-};
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
 // Rows of the walk graph.
 // ---------------------------------------------------------------------------
-// off[x] = the first sorted position whose tail is >= x; off[n] = E.
-__global__ void k_row_offsets(const uint32_t *ks, long long E, long long n, long long *off)
+// off[x] = the first sorted position whose tail is >= x; off[n] = E.  Clears the counters of k_rows.
+__global__ void __launch_bounds__(256) k_row_offsets(const uint32_t *ks, long long E, long long n, long long *off,
+                                                     unsigned long long *cnt)
 {
-    long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= E) return;
-    const long long k = ks[i];
-    const long long prev = i == 0 ? -1 : (long long)ks[i - 1];
-    for (long long x = prev + 1; x <= k; ++x) off[x] = i;
-    if (i == E - 1)
-        for (long long x = k + 1; x <= n; ++x) off[x] = E;
-}
-
-__global__ void k_rows(const long long *off, long long n, long long *start, long long *len)
-{
-    long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= n) return;
-    start[x] = off[x];
-    len[x] = off[x + 1] - off[x];
-}
-
-__global__ void k_entry_weights(const float *ws, long long E, double *s0)
-{
-    long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < E) s0[i] = (double)ws[i];
-}
-
-// q = fl(fl(w len) / W) with W the row's scanned total; a row whose total is not a
-// positive finite number makes every item heavy (prob 1, itself).  Light flag into light (and 0
-// behind the last).
-__global__ void k_row_normalise(const uint32_t *ks, const float *ws, const long long *off, const double *scan, long long E,
-                                double *q, uint32_t *light)
-{
-    long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == E) light[E] = 0u;
-    if (i >= E) return;
-    const long long x = ks[i], lo = off[x], hi = off[x + 1];
-    const double W = scan[hi - 1];
-    const bool ok = W > 0.0 && !isinf(W);
-    const double qi = ok ? __ddiv_rn(__dmul_rn((double)ws[i], (double)(hi - lo)), W) : 1.0;
-    q[i] = qi;
-    light[i] = qi < 1.0 ? 1u : 0u;
-}
-
-// Lights of row x to [lo, lo + nL) and heavies to [lo + nL, hi), each in index order.
-__global__ void k_row_split(const uint32_t *ks, const long long *off, const double *q, Counts lights, long long E,
-                            double *dx, int32_t *idx)
-{
-    long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= E) return;
-    const long long x = ks[i], lo = off[x], base = lights.before(lo);
-    const long long nL = lights.before(off[x + 1]) - base, a = lights.before(i) - base;
-    const double qi = q[i];
-    if (qi < 1.0) {
-        dx[lo + a] = __dsub_rn(1.0, qi);
-        idx[lo + a] = (int32_t)(i - lo);
-    } else {
-        const long long k = (i - lo) - a;
-        dx[lo + nL + k] = __dsub_rn(qi, 1.0);
-        idx[lo + nL + k] = (int32_t)(i - lo);
+    if (blockIdx.x == 0 && threadIdx.x < 3) cnt[threadIdx.x] = 0ull;
+    const long long i0 = (long long)blockIdx.x * 1024 + threadIdx.x;
+    long long k[4], prev[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const long long i = i0 + r * 256 < E ? i0 + r * 256 : E - 1;
+        k[r] = ks[i];
+        prev[r] = i == 0 ? -1 : (long long)ks[i - 1];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const long long i = i0 + r * 256;
+        if (i >= E) break;
+        for (long long x = prev[r] + 1; x <= k[r]; ++x) off[x] = i;
+        if (i == E - 1)
+            for (long long x = k[r] + 1; x <= n; ++x) off[x] = E;
     }
 }
 
-// Sub-rows: lights of x at 2x, heavies at 2x + 1.
-__global__ void k_subrows(const long long *off, Counts lights, long long n, long long *start, long long *len)
-{
-    long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= n) return;
-    const long long lo = off[x], hi = off[x + 1];
-    const long long nL = hi > lo ? lights.before(hi) - lights.before(lo) : 0;
-    start[2 * x] = lo;
-    len[2 * x] = nL;
-    start[2 * x + 1] = lo + nL;
-    len[2 * x + 1] = hi - lo - nL;
-}
+// The chain of one short row (values in LDS, one chunk) by one thread, eight values at a time; the
+// errors as in block_chains.  SCAN: each value becomes the running maximum of s + c; otherwise only
+// the total s + c is wanted, and returned.
+struct RowChain {
+    double s, c, m;
 
-__device__ __forceinline__ unsigned long long walk_thr(double prob)
-{
-    if (prob >= 1.0) return ~0ull;
-    return (unsigned long long)__dmul_rn(prob, 18446744073709551616.0);
-}
-
-__device__ __forceinline__ long long walk_count_le(const double *X, long long nH, double s)
-{
-    long long lo = 0, hi = nH;
-    while (lo < hi) {
-        long long mid = lo + (hi - lo) / 2;
-        if (X[mid] <= s)
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    return lo;
-}
-
-__device__ __forceinline__ long long walk_count_start_lt(const double *D, long long nL, double x)
-{
-    if (nL == 0 || !(0.0 < x)) return 0;
-    long long lo = 0, hi = nL - 1;
-    while (lo < hi) {
-        long long mid = lo + (hi - lo) / 2;
-        if (D[mid] < x)
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    return 1 + lo;
-}
-
-// The closed form of the sweeping construction (alias.hip) within row x, for the item at
-// sorted position j of the light/heavy split.  Writes the item's record.
-__global__ void k_row_records(const uint32_t *ks, const uint32_t *hs, const long long *off, Counts lights,
-                              const double *q, const double *dx, const int32_t *idx, long long E, WalkRec *rec)
-{
-    long long j = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= E) return;
-    const long long x = ks[j], lo = off[x], hi = off[x + 1], len = hi - lo;
-    const long long nL = lights.before(hi) - lights.before(lo), nH = len - nL;
-    const double *D = dx + lo, *X = dx + lo + nL;
-    const int32_t *I = idx + lo;
-    const long long a = j - lo;
-    const long long item = I[a];
-    unsigned long long thr = ~0ull;
-    long long al = item;
-    if (a < nL) {
-        if (nH > 0) {
-            const double S = a == 0 ? 0.0 : D[a - 1];
-            long long k = walk_count_le(X, nH, S);
-            if (k > nH - 1) k = nH - 1;
-            thr = walk_thr(q[lo + item]);
-            al = I[nL + k];
+    template <bool SCAN>
+    __device__ __forceinline__ void eight(double (&v)[8])
+    {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const double p = s;
+            s = p + v[k];
+            const double b = s - p;
+            c += (p - (s - b)) + (v[k] - b);
+            if (SCAN) v[k] = m = __builtin_fmax(m, s + c);
         }
-    } else {
-        const long long k = a - nL;
-        if (k < nH - 1) {
-            const long long jj = walk_count_start_lt(D, nL, X[k]) - 1;
-            double ov = 0.0;
-            if (jj >= 0) {
-                ov = __dsub_rn(D[jj], X[k]);
+    }
+};
+
+template <bool SCAN>
+__device__ __forceinline__ double row_chain(double *x, int n)
+{
+    RowChain r{0.0, 0.0, -__builtin_huge_val()};
+    int k0 = 0;
+    for (; k0 + 8 <= n; k0 += 8) {
+        double v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = x[k0 + k];
+        r.eight<SCAN>(v);
+        if (SCAN) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) x[k0 + k] = v[k];
+        }
+    }
+    if (k0 < n) {
+        double v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            v[k] = x[k0 + k < n ? k0 + k : k0];
+            if (k0 + k >= n) v[k] = 0.0;
+        }
+        r.eight<SCAN>(v);
+        if (SCAN) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (k0 + k < n) x[k0 + k] = v[k];
+        }
+    }
+    return r.s + r.c;
+}
+
+// Items of 256 threads' flags, 8 per thread (thread t has items t, 256 + t, ..): flags before each
+// group of 64 items go to at[r][wave]; the total is returned.
+constexpr int ROW_WINDOW = 2048, ROW_TILE = ROW_WINDOW - ROW_SHORT, ROW_PER = ROW_WINDOW / 256;
+
+__device__ __forceinline__ int flag_groups(const unsigned long long (&mask)[ROW_PER], uint16_t *at)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int r = 0; r < ROW_PER; ++r)
+        if (lane == r) at[r * 4 + wave] = (uint16_t)__popcll(mask[r]);
+    __syncthreads();
+    // (every wavefront for itself: lane g sums the groups up to g)
+    const int own = lane < 4 * ROW_PER ? at[lane] : 0;
+    int inc = own;
+#pragma unroll
+    for (int d = 1; d < 4 * ROW_PER; d <<= 1) {
+        const int y = __shfl_up(inc, d);
+        if (lane >= d) inc += y;
+    }
+    __syncthreads();
+    if (wave == 0 && lane < 4 * ROW_PER) at[lane] = (uint16_t)(inc - own);
+    __syncthreads();
+    return __shfl(inc, 4 * ROW_PER - 1);
+}
+
+// Records of the rows that start among this workgroup's ROW_TILE sorted entries and are at most
+// ROW_SHORT long, in LDS from the weights to the records, which are written in order; longer rows are only
+// listed.  A thread runs a row's chain, then a light or heavy half's.
+//
+// What bounds it is the instructions of the chains (a wavefront runs as long as its longest row) and
+// of the entries' divisions and searches.  The limit of 256 entries and the tile of 1,792 (a window
+// of 2,048) keep the one small and fill the lanes: 33.6 M entries in 0.57 ms, with rows of up to
+// 1,024 and tiles of 1,024 in 0.96 ms.  The longer rows, which need 0.95 ms there, took 1.5 ms a
+// workgroup each.  A kernel per step over all rows (a thread per chain in memory, three scans with
+// their offsets written out) took 4.1 ms for all rows.
+__global__ void __launch_bounds__(256) k_rows(const uint32_t *ks, const float *ws, const uint32_t *hs, const long long *off,
+                                              long long E, WalkRec *rec, LongRow *rows, uint32_t *huge,
+                                              uint32_t *slot_row, unsigned long long *cnt)
+{
+    __shared__ double v[ROW_WINDOW];      // weights, then per row deficits and excesses, then their scans
+    __shared__ uint16_t idx[ROW_WINDOW];  // at a heavy's place in the split: its entry
+    __shared__ uint16_t start[ROW_TILE], len[ROW_TILE], lights[ROW_TILE + 1];  // per row; lights before it
+    __shared__ uint16_t at[4 * ROW_PER];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const long long p0 = (long long)blockIdx.x * ROW_TILE;
+    const int owned = (int)(E - p0 < ROW_TILE ? E - p0 : ROW_TILE), here = (int)(E - p0 < ROW_WINDOW ? E - p0 : ROW_WINDOW);
+    // entry r of this thread: r * 256 + threadIdx.x
+    float w[ROW_PER];
+    uint32_t key[ROW_PER], prev[ROW_PER];
+    unsigned long long mask[ROW_PER];
+#pragma unroll
+    for (int r = 0; r < ROW_PER; ++r) {
+        const int i = r * 256 + (int)threadIdx.x;
+        const long long p = p0 + (i < here ? i : here - 1);
+        w[r] = ws[p];
+        key[r] = ks[p];
+        prev[r] = ks[p > 0 ? p - 1 : 0];
+    }
+#pragma unroll
+    for (int r = 0; r < ROW_PER; ++r) {
+        const int i = r * 256 + (int)threadIdx.x;
+        mask[r] = __ballot(i < owned && (p0 + i == 0 || prev[r] != key[r]));
+        v[i] = (double)w[r];
+    }
+    const int nrows = flag_groups(mask, at);
+    int row[ROW_PER];
+#pragma unroll
+    for (int r = 0; r < ROW_PER; ++r) {
+        const int i = r * 256 + (int)threadIdx.x;
+        const bool head = (mask[r] >> lane) & 1ull;
+        row[r] = at[r * 4 + wave] + __popcll(mask[r] & below) + (head ? 1 : 0) - 1;
+        if (!head) continue;
+        const long long lo = p0 + i, n = off[key[r] + 1] - lo;
+        start[row[r]] = (uint16_t)i;
+        len[row[r]] = n <= ROW_SHORT ? (uint16_t)n : (uint16_t)0;
+        if (n > ROW_SHORT) {
+            const unsigned long long slots = LH_CDIV(n, SCAN_CHUNK) + 1;
+            const unsigned long long k = atomicAdd(&cnt[0], 1ull), s = atomicAdd(&cnt[1], slots);
+            rows[k] = LongRow{lo, n, (long long)s, 0.0};
+            if (n > ROW_HUGE) huge[atomicAdd(&cnt[2], 1ull)] = (uint32_t)k;
+            for (unsigned long long j = 0; j < slots; ++j) slot_row[s + j] = (uint32_t)k;
+        }
+    }
+    __syncthreads();
+    for (int x = threadIdx.x; x < nrows; x += 256) {
+        const int n = len[x];
+        if (n > 0) {
+            const double W = row_chain<false>(v + start[x], n);
+            v[start[x]] = W;  // (the weights are in registers)
+        }
+    }
+    __syncthreads();
+    double q[ROW_PER];
+    bool mine[ROW_PER];
+#pragma unroll
+    for (int r = 0; r < ROW_PER; ++r) {
+        const int i = r * 256 + (int)threadIdx.x;
+        const int x = row[r] < 0 ? 0 : row[r], n = len[x], j = i - start[x];
+        mine[r] = row[r] >= 0 && j < n;
+        q[r] = mine[r] ? alias_q((double)w[r], n, v[start[x]]) : 1.0;
+        mask[r] = __ballot(q[r] < 1.0);
+    }
+    const int nlights = flag_groups(mask, at);
+    if (threadIdx.x == 0) lights[nrows] = (uint16_t)nlights;
+    int a[ROW_PER];  // lights before the entry
+#pragma unroll
+    for (int r = 0; r < ROW_PER; ++r) {
+        const int i = r * 256 + (int)threadIdx.x;
+        a[r] = at[r * 4 + wave] + __popcll(mask[r] & below);
+        if (row[r] >= 0 && i == start[row[r]]) lights[row[r]] = (uint16_t)a[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ROW_PER; ++r) {
+        if (!mine[r]) continue;
+        const int i = r * 256 + (int)threadIdx.x, s = start[row[r]], l0 = lights[row[r]], nL = lights[row[r] + 1] - l0;
+        a[r] -= l0;
+        if (q[r] < 1.0) {
+            v[s + a[r]] = __dsub_rn(1.0, q[r]);
+        } else {
+            const int p = s + nL + (i - s - a[r]);
+            v[p] = __dsub_rn(q[r], 1.0);
+            idx[p] = (uint16_t)i;
+        }
+    }
+    __syncthreads();
+    for (int x = threadIdx.x; x < 2 * nrows; x += 256) {
+        const int n = len[x >> 1], nL = n > 0 ? lights[(x >> 1) + 1] - lights[x >> 1] : 0;
+        double *const d = v + start[x >> 1] + (x & 1 ? nL : 0);
+        (void)row_chain<true>(d, x & 1 ? n - nL : nL);
+    }
+    __syncthreads();
+    // Searches, in step for all of a thread's entries: a light's start S = D[a - 1] among the row's
+    // excesses, a heavy's X[k] among its deficits but the last.
+    int lo[ROW_PER], hi[ROW_PER], base[ROW_PER], most = 0;
+    double s[ROW_PER];
+#pragma unroll
+    for (int r = 0; r < ROW_PER; ++r) {
+        lo[r] = hi[r] = base[r] = 0;
+        s[r] = 0.0;
+        if (!mine[r]) continue;
+        const int i = r * 256 + (int)threadIdx.x, st = start[row[r]], n = len[row[r]],
+                  nL = lights[row[r] + 1] - lights[row[r]];
+        const bool light = q[r] < 1.0;
+        base[r] = light ? st + nL : st;
+        if (light) {
+            hi[r] = n - nL;
+            s[r] = a[r] > 0 ? v[st + a[r] - 1] : 0.0;
+        } else {
+            s[r] = v[st + nL + (i - st - a[r])];
+            hi[r] = nL > 0 && 0.0 < s[r] ? nL - 1 : 0;
+        }
+        most = hi[r] > most ? hi[r] : most;
+    }
+    for (; most > 0; most >>= 1) {
+#pragma unroll
+        for (int r = 0; r < ROW_PER; ++r) {
+            const int mid = (lo[r] + hi[r]) >> 1;
+            const double y = v[base[r] + mid];
+            const bool open = lo[r] < hi[r], up = q[r] < 1.0 ? y <= s[r] : y < s[r];
+            if (open && up) lo[r] = mid + 1;
+            else if (open) hi[r] = mid;
+        }
+    }
+    unsigned long long thr[ROW_PER];
+    int alias[ROW_PER];
+#pragma unroll
+    for (int r = 0; r < ROW_PER; ++r) {
+        thr[r] = ~0ull;
+        alias[r] = r * 256 + (int)threadIdx.x;
+        if (!mine[r]) continue;
+        const int i = alias[r], st = start[row[r]], n = len[row[r]], nL = lights[row[r] + 1] - lights[row[r]], nH = n - nL;
+        if (q[r] < 1.0) {
+            if (nH > 0) {
+                thr[r] = prob_to_thr(q[r]);
+                alias[r] = idx[st + nL + (lo[r] < nH - 1 ? lo[r] : nH - 1)];
+            }
+        } else {
+            const int k = i - st - a[r];
+            if (k < nH - 1 && nL > 0 && 0.0 < s[r]) {
+                double ov = __dsub_rn(v[st + lo[r]], s[r]);
                 if (ov < 0.0) ov = 0.0;
-            }
-            if (ov > 0.0) {
-                const double p = __dsub_rn(1.0, ov);
-                thr = walk_thr(p < 0.0 ? 0.0 : p);
-                al = I[nL + k + 1];
+                if (ov > 0.0) {
+                    const double p = __dsub_rn(1.0, ov);
+                    thr[r] = prob_to_thr(p < 0.0 ? 0.0 : p);
+                    alias[r] = idx[st + nL + k + 1];
+                }
             }
         }
     }
-    WalkRec r;
-    r.thr = thr;
-    r.keep = (int32_t)hs[lo + item];
-    r.alias = (int32_t)hs[lo + al];
-    rec[lo + item] = r;
+    int32_t keep[ROW_PER], other[ROW_PER];
+#pragma unroll
+    for (int r = 0; r < ROW_PER; ++r) {
+        const int i = r * 256 + (int)threadIdx.x;
+        keep[r] = (int32_t)hs[p0 + (i < here ? i : 0)];
+        other[r] = (int32_t)hs[p0 + (i < here ? alias[r] : 0)];
+    }
+#pragma unroll
+    for (int r = 0; r < ROW_PER; ++r)
+        if (mine[r]) rec[p0 + r * 256 + threadIdx.x] = WalkRec{thr[r], keep[r], other[r]};
+}
+
+// The long rows as a set of tables (table.hpp): a workgroup per slot, so a row has one for each
+// chunk of its entries and one more.
+struct RowTable : Table {
+    const uint32_t *heads;
+    WalkRec *rec;
+
+    __device__ __forceinline__ double q(long long i, double Wt) const { return alias_q((double)w[i], N, Wt); }
+    template <int RS>
+    __device__ __forceinline__ void write(long long first, long long end, const unsigned long long (&thr)[RS],
+                                          const uint32_t (&al)[RS]) const
+    {
+        int32_t keep[RS], other[RS];
+#pragma unroll
+        for (int r = 0; r < RS; ++r) {
+            const long long i = first + r * 64;
+            keep[r] = (int32_t)heads[i < end ? i : end - 1];
+            other[r] = (int32_t)heads[i < end ? (long long)al[r] : end - 1];
+        }
+#pragma unroll
+        for (int r = 0; r < RS; ++r)
+            if (first + r * 64 < end) rec[first + r * 64] = WalkRec{thr[r], keep[r], other[r]};
+    }
+};
+
+struct LongRows {
+    LongRow *rows;
+    const uint32_t *huge;
+    const uint32_t *slot_row;
+    const float *ws;
+    const uint32_t *hs;
+    WalkRec *rec;
+    double *dx;
+    uint32_t *idx, *blk;
+    double *tot, *mxl, *off, *before;
+
+    __device__ __forceinline__ RowTable whole(unsigned k) const
+    {
+        const long long lo = rows[k].lo, s = rows[k].slot;
+        RowTable t;
+        t.N = rows[k].len;
+        t.w = ws + lo;
+        t.dx = dx + lo;
+        t.idx = idx + lo;
+        t.blk = blk + s;
+        t.tot = tot + s;
+        t.mxl = mxl + s;
+        t.off = off + s;
+        t.before = before + s;
+        t.W = &rows[k].W;
+        t.heads = hs + lo;
+        t.rec = rec + lo;
+        return t;
+    }
+    __device__ __forceinline__ RowTable of(long long &b) const
+    {
+        const uint32_t k = slot_row[blockIdx.x];
+        b = (long long)blockIdx.x - rows[k].slot;
+        return whole(k);
+    }
+};
+
+__global__ void __launch_bounds__(256) k_row_records(LongRows T)
+{
+    __shared__ RecLds lds;
+    long long b;
+    const RowTable t = T.of(b);
+    const long long left = t.N - b * REC_ITEMS;
+    if (left <= 0) return;
+    if (left <= 256) records_run<1>(t, b, lds);
+    else if (left <= 512) records_run<2>(t, b, lds);
+    else if (left <= 768) records_run<3>(t, b, lds);
+    else records_run<4>(t, b, lds);
+}
+
+// The rows longer than ROW_HUGE alone, for what takes a workgroup a row or half a row.
+struct HugeRows {
+    LongRows T;
+    __device__ __forceinline__ RowTable whole(unsigned k) const { return T.whole(T.huge[k]); }
+};
+
+__global__ void __launch_bounds__(LEVEL_THREADS) k_huge_weights(HugeRows T)
+{
+    __shared__ LevelLds l;
+    (void)levels_weight(T.whole(blockIdx.x), l);
+}
+
+// Chains of 16 slots' chunks, of whatever rows: most long rows have one or two chunks, so a
+// workgroup to a row would run one chain where it can run 16 in the same time.  Chunk j of a row's
+// weights is in its slot j; of its deficits too, with the excesses' chunks behind them.
+__global__ void __launch_bounds__(256) k_row_chain_weights(LongRows T, long long slots)
+{
+    __shared__ double lds[CHAIN_LDS];
+    __shared__ ChainSegs segs;
+    const long long s0 = (long long)blockIdx.x * WAVE_CHUNKS, s = s0 + threadIdx.x;
+    if (threadIdx.x < WAVE_CHUNKS) {
+        long long at = 0, left = 0;
+        if (s < slots) {
+            const LongRow &r = T.rows[T.slot_row[s]];
+            at = (s - r.slot) * SCAN_CHUNK;
+            left = r.len - at;
+            at = r.lo + (left > 0 ? at : 0);
+        }
+        segs.start[threadIdx.x] = at;
+        segs.len[threadIdx.x] = left <= 0 ? 0 : left < SCAN_CHUNK ? (int)left : SCAN_CHUNK;
+    }
+    __syncthreads();
+    const float *ws = T.ws;
+    double *tot = T.tot;
+    block_chains<0, float>(lds, segs, [&](long long i) { return ws[i]; }, [](long long, double) {},
+                           [&](int r, double v) { if (segs.len[r]) tot[s0 + r] = v; }, [](int, double) {});
+}
+
+__global__ void __launch_bounds__(256, 4) k_row_chain_dx(LongRows T, long long slots)
+{
+    __shared__ double lds[CHAIN_LDS];
+    __shared__ ChainSegs segs;
+    const long long s0 = (long long)blockIdx.x * WAVE_CHUNKS, s = s0 + threadIdx.x;
+    if (threadIdx.x < WAVE_CHUNKS) {
+        long long at = 0, left = 0;
+        if (s < slots) {
+            const LongRow &r = T.rows[T.slot_row[s]];
+            const long long nL = T.blk[r.slot + LH_CDIV(r.len, SPLIT_ITEMS)], cL = LH_CDIV(nL, SCAN_CHUNK), j = s - r.slot;
+            const long long first = j < cL ? j * SCAN_CHUNK : nL + (j - cL) * SCAN_CHUNK;
+            left = (j < cL ? nL : r.len) - first;
+            at = r.lo + (left > 0 ? first : 0);
+        }
+        segs.start[threadIdx.x] = at;
+        segs.len[threadIdx.x] = left <= 0 ? 0 : left < SCAN_CHUNK ? (int)left : SCAN_CHUNK;
+    }
+    __syncthreads();
+    double *x = T.dx, *tot = T.tot, *mxl = T.mxl;
+    block_chains<2, double>(lds, segs, [&](long long i) { return x[i]; }, [&](long long i, double v) { x[i] = v; },
+                            [&](int r, double v) { if (segs.len[r]) tot[s0 + r] = v; },
+                            [&](int r, double v) { if (segs.len[r]) mxl[s0 + r] = v; });
+}
+
+// What levels_weight, k_split_scan and k_levels_dx do, for rows of at most 64 chunks: a wavefront
+// a row or half a row, lane l has chunk l.
+__device__ __forceinline__ double lane_chain(double x, int n)
+{
+    OpNeumaier::State st = OpNeumaier::init();
+    double mine = 0.0;
+    for (int i = 0; i < n; ++i) {
+        const double v = OpNeumaier::step(st, __shfl(x, i));
+        if ((int)(threadIdx.x & 63) == i) mine = v;
+    }
+    return mine;
+}
+
+__global__ void __launch_bounds__(256) k_row_weights(LongRows T, unsigned rows)
+{
+    const unsigned k = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (k >= rows || T.rows[k].len > ROW_HUGE) return;
+    const RowTable t = T.whole(k);
+    const int nch = (int)LH_CDIV(t.N, SCAN_CHUNK);
+    const double x = lane < nch ? t.tot[lane] : 0.0;
+    const double before = __shfl(lane_chain(x, nch - 1), nch > 1 ? nch - 2 : 0), last = __shfl(x, nch - 1);
+    if (lane == 0) *t.W = nch > 1 ? OpNeumaier::combine(before, last) : last;
+}
+
+__global__ void __launch_bounds__(256) k_row_split_scan(LongRows T, unsigned rows)
+{
+    const unsigned k = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (k >= rows || T.rows[k].len > ROW_HUGE) return;
+    const RowTable t = T.whole(k);
+    const int nt = (int)LH_CDIV(t.N, SPLIT_ITEMS);
+    const uint32_t c = lane < nt ? t.blk[lane] : 0u;
+    uint32_t inc = c;
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t y = __shfl_up(inc, d);
+        if (lane >= d) inc += y;
+    }
+    if (lane < nt) t.blk[lane] = inc - c;
+    if (lane == 63) t.blk[nt] = inc;
+}
+
+__global__ void __launch_bounds__(256) k_row_levels_dx(LongRows T, unsigned rows)
+{
+    const unsigned g = blockIdx.x * 4 + (threadIdx.x >> 6), k = g >> 1;
+    const int lane = threadIdx.x & 63;
+    if (k >= rows || T.rows[k].len > ROW_HUGE) return;
+    const RowTable t = T.whole(k);
+    const bool heavy = (g & 1u) != 0;
+    const long long nL = t.lights(), c0 = heavy ? LH_CDIV(nL, SCAN_CHUNK) : 0;
+    const int nch = (int)LH_CDIV(heavy ? t.N - nL : nL, SCAN_CHUNK);
+    if (nch == 0) return;
+    const double x = lane < nch ? t.tot[c0 + lane] : 0.0, none = -__builtin_huge_val();
+    double off = __shfl_up(lane_chain(x, nch - 1), 1);
+    if (lane == 0) off = 0.0;
+    double m = lane < nch ? off + t.mxl[c0 + lane] : none;
+    for (int d = 1; d < 64; d <<= 1) {
+        const double y = __shfl_up(m, d);
+        if (lane >= d) m = __builtin_fmax(m, y);
+    }
+    double before = __shfl_up(m, 1);
+    if (lane == 0) before = none;
+    if (lane >= nch) return;
+    t.off[c0 + lane] = off;
+    t.before[c0 + lane] = before;
+    t.mxl[c0 + lane] = m;
 }
 
 // ---------------------------------------------------------------------------
@@ -361,40 +692,54 @@ static lh_status build_walk(lh_handle *h, char *persist, char *scratch, const Wa
     w.pairs = (int2 *)(persist + WL.pairs);
     const auto words = [&](size_t at) { return (uint32_t *)(scratch + at); };
     const SortBuffers b0{words(S.k0), words(S.w0), words(S.h0)}, b1{words(S.k1), words(S.w1), words(S.h1)};
-    double *s0 = (double *)(scratch + S.s0), *q = (double *)(scratch + S.q);
-    long long *sstart = (long long *)(scratch + S.sstart), *slen = (long long *)(scratch + S.slen);
-    Arena ar;
-    ar.base = scratch + S.arena;
-    ar.bytes = S.arena_bytes;
-    const dim3 blk(256), ge((unsigned)LH_CDIV(E, 256)), ge1((unsigned)LH_CDIV(E + 1, 256)), gn((unsigned)LH_CDIV(n, 256));
-
     int bits = 1;
     while (bits < 31 && (1ll << bits) < n) ++bits;
     const SortBuffers rows = radix_sort(WalkEntries{h->src, h->dst, h->w, (unsigned long long)m}, E, bits, b0, b1,
                                         words(S.hist), words(S.part), st);
-    // the other buffers of the sort: light counts and the split's item indices
     const SortBuffers rest = rows.k == b0.k ? b1 : b0;
     const uint32_t *ks = rows.k, *hs = rows.p1;
     const float *ws = (const float *)rows.p0;
-    uint32_t *light = rest.k;
-    int32_t *idx = (int32_t *)rest.p0;
-    const Counts lights{light, words(S.part)};
+    unsigned long long *cnt = (unsigned long long *)(scratch + S.cnt);
+    LongRows T;
+    T.rows = (LongRow *)(scratch + S.rows);
+    T.huge = words(S.huge);
+    T.slot_row = words(S.slot_row);
+    T.ws = ws;
+    T.hs = hs;
+    T.rec = w.rec;
+    // in the sort's other buffers (both payloads together hold E binary64 values)
+    T.dx = (double *)rest.p0;
+    T.idx = rest.k;
+    T.blk = words(S.blk);
+    T.tot = (double *)(scratch + S.tot);
+    T.mxl = (double *)(scratch + S.mxl);
+    T.off = (double *)(scratch + S.off);
+    T.before = (double *)(scratch + S.before);
 
-    hipLaunchKernelGGL(k_row_offsets, ge, blk, 0, st, ks, E, n, w.off);
-    hipLaunchKernelGGL(k_rows, gn, blk, 0, st, w.off, n, sstart, slen);
-    hipLaunchKernelGGL(k_entry_weights, ge, blk, 0, st, ws, E, s0);
-    hipError_t e = seg_scan<OpNeumaier>(s0, E, sstart, slen, n, ar, st);
-    if (e != hipSuccess) return hip_fail(h, e, "walk rows: weight scan");
-    hipLaunchKernelGGL(k_row_normalise, ge1, blk, 0, st, ks, ws, w.off, s0, E, q, light);
-    const unsigned np = (unsigned)LH_CDIV(E + 1, (long long)SORT_TILE);
-    hipLaunchKernelGGL(k_sort_scan, dim3(np), dim3(SORT_THREADS), 0, st, light, (unsigned long long)E + 1, words(S.part));
-    hipLaunchKernelGGL(k_sort_parts, dim3(1), dim3(1024), 0, st, words(S.part), np);
-    hipLaunchKernelGGL(k_row_split, ge, blk, 0, st, ks, w.off, q, lights, E, s0, idx);
-    hipLaunchKernelGGL(k_subrows, gn, blk, 0, st, w.off, lights, n, sstart, slen);
-    e = seg_scan<OpNeumaier>(s0, E, sstart, slen, 2 * n, ar, st);
-    if (e == hipSuccess) e = seg_scan<OpMax>(s0, E, sstart, slen, 2 * n, ar, st);
-    if (e != hipSuccess) return hip_fail(h, e, "walk rows: deficit and excess scans");
-    hipLaunchKernelGGL(k_row_records, ge, blk, 0, st, ks, hs, w.off, lights, q, s0, idx, E, w.rec);
+    hipLaunchKernelGGL(k_row_offsets, dim3((unsigned)LH_CDIV(E, 1024)), dim3(256), 0, st, ks, E, n, w.off, cnt);
+    hipLaunchKernelGGL(k_rows, dim3((unsigned)LH_CDIV(E, ROW_TILE)), dim3(256), 0, st, ks, ws, hs, w.off, E, w.rec, T.rows,
+                       words(S.huge), words(S.slot_row), cnt);
+    unsigned long long listed[3];  // long rows, their slots, huge rows
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(listed, cnt, sizeof(listed), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return hip_fail(h, e, "walk rows");
+    if (listed[0] == 0) return LH_OK;
+    const unsigned nr = (unsigned)listed[0], nh = (unsigned)listed[2];
+    const long long slots = (long long)listed[1];
+    const HugeRows H{T};
+    const dim3 gs((unsigned)slots), gc((unsigned)LH_CDIV(slots, WAVE_CHUNKS)), gr((unsigned)LH_CDIV(nr, 4)), blk(256);
+    hipLaunchKernelGGL(k_row_chain_weights, gc, blk, 0, st, T, slots);
+    hipLaunchKernelGGL(k_row_weights, gr, blk, 0, st, T, nr);
+    if (nh) hipLaunchKernelGGL(k_huge_weights, dim3(nh), blk, 0, st, H);
+    hipLaunchKernelGGL(k_split_count<LongRows>, gs, blk, 0, st, T);
+    hipLaunchKernelGGL(k_row_split_scan, gr, blk, 0, st, T, nr);
+    if (nh) hipLaunchKernelGGL(k_split_scan<HugeRows>, dim3(nh), dim3(1024), 0, st, H);
+    hipLaunchKernelGGL(k_split<LongRows>, gs, blk, 0, st, T);
+    hipLaunchKernelGGL(k_row_chain_dx, gc, blk, 0, st, T, slots);
+    hipLaunchKernelGGL(k_row_levels_dx, dim3((unsigned)LH_CDIV(nr, 2)), blk, 0, st, T, nr);
+    if (nh) hipLaunchKernelGGL(k_levels_dx<HugeRows>, dim3(2 * nh), blk, 0, st, H);
+    hipLaunchKernelGGL(k_row_records, gs, blk, 0, st, T);
     e = hipStreamSynchronize(st);
     if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "walk rows");
