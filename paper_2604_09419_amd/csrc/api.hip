@@ -55,6 +55,9 @@ GraphDev graph_dev(const lh_handle *h)
     g.slot = shadowed ? sc.slot : nullptr;
     g.tiles = h->ws ? (unsigned long long *)(h->ws + h->lay.tiles) : nullptr;
     g.tile_shift = 6;
+    g.streams = 0;
+    g.q_shift = 0;
+    g.laps = 0;
     g.pairs = nullptr;
     g.pairs_first = 0;
     g.heat = h->ws ? (const uint8_t *)(h->ws + h->lay.nheat) : nullptr;

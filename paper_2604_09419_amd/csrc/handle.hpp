@@ -38,6 +38,11 @@ struct GraphDev {
     // wavefronts take tiles of 2^tile_shift samples from it until none are left.
     unsigned long long *tiles;
     int tile_shift;
+    // Launches of wavefront teams (four_unit_lanes): streams of tiles (0: no teams), log2 of a team's
+    // wavefronts, and laps, in each of which every team takes tiles of its stream.
+    unsigned streams;
+    int q_shift;
+    unsigned long long laps;
     // Positive pairs from random walks: pairs[s - pairs_first] is the (u, v) of sample s
     // (every sample of the launch lies in the buffer); NULL: slot 0 draws an arc.  heat:
     // per-node heat, for the write path of a walk pair's rows.
@@ -200,14 +205,26 @@ constexpr double kTwoPerWaveMaxHotShare = 0.1;
 // 33 to 64 units: (32, 2) (150,000 nodes: 1.76 against 1.78 for (64, 1) and 2.37 for (16, 4)).
 constexpr double kCachedTableBytes = 512.0 * 1048576.0;
 // Tables that fit in one L2 have every row updated atomically: no update is lost, and what a run
-// ends with depends on staleness alone.  There, one or two units a lane keep a sample between its
-// loads and its writes for most of a round, where four units a lane spend the round issuing
-// accesses, so at the same number of resident samples, which is what the cap counts, they are
-// several times as stale: 10,000 nodes at d = 16 train in 6.1 ns a sample but end 2-3 % (Frobenius)
-// from where four units a lane end (28 ns), whose own runs differ by 0.3-0.5 %.  Filling this
-// share of the cap, they end 0.5-1 % off in 14.3 ns.  At other widths such a share leaves no gain
-// over four units a lane (d = 32: 15.2 against 14.8 ns; d = 64: 13.0 against 8.3), which they keep.
-constexpr double kSmallTableCapShare = 0.4;
+// ends with depends on the order in which samples are taken.  With four units a lane (few lanes a
+// sample, many samples a wavefront) a binary32 launch spends its rounds issuing accesses; with one
+// unit a lane, at the same number of samples in flight, which is what the cap counts, a sample takes
+// a fourth of the time, but there are four times as many wavefronts, and with a tile of 64
+// consecutive samples each, samples are taken out of order over four times as long a window: runs
+// then ended 2-15 % (Frobenius) from where four units a lane end, whose own runs differ by
+// 0.3-0.5 %, whatever the samples in flight.  So 2^q_shift wavefronts share the tiles that one
+// wavefront of the narrow shape would take, each a share of every round and in step with the others
+// of its workgroup, and the samples are taken in its order.  10,000 nodes, 10^6 samples, narrow and
+// wide: d = 16 28.3 and 5.7 ms for (16, 1), d = 32 14.7 and 6.4 for (16, 2), d = 64 8.3 and 6.1 for
+// (32, 2); 3,500 nodes, 300,000 samples, d = 128 5.7 and 4.3 for (64, 2).  They end 0.4-0.9 % from
+// where the narrow shape ends (0.5-1.2 % with wavefronts out of step), and one unit a lane for wider
+// rows 0.6-1.4 % (d = 32 in 5.5 ms, d = 64 in 5.9).
+// Lanes per sample of the shape with four units a lane.
+inline int four_unit_lanes(int nunits)
+{
+    int l = 2;
+    while (l < 64 && 4 * l < nunits) l *= 2;
+    return l;
+}
 // A launch keeps no more samples in flight than the graph's hottest row can serve: its updates are
 // atomics on the same lines, one after the other (24 ns per 256 bytes), so with p_max the
 // probability that a sample touches it, more than about latency / (p_max x that time) samples

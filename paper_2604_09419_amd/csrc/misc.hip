@@ -96,13 +96,8 @@ TileCfg natural_cfg(int dtype, int d)
 {
     const int nu = units_per_row(dtype, d);
     TileCfg c;
-    c.lps = next_pow2(LH_CDIV(nu, 4));
-    if (c.lps < 2) c.lps = 2;
-    c.upl = 4;
-    if (c.lps > 64) {
-        c.lps = 64;
-        c.upl = 8;
-    }
+    c.lps = four_unit_lanes(nu);
+    c.upl = nu <= 256 ? 4 : 8;
     c.blocks_per_cu = 8;
     return c;
 }
@@ -161,7 +156,14 @@ static TileCfg auto_cfg_f32(const lh_handle *h, const TileCfg &wide)
     const double bytes = tables_bytes(h);
     TileCfg c = wide;
     if (small_table_window(h->l2_bytes, bytes) > 0.0) {
-        if (nu != 16) c = natural_cfg(h->p.dtype, h->p.d);
+        c = natural_cfg(h->p.dtype, h->p.d);  // four units a lane, or teams of narrower lanes
+        if (nu <= 16) {
+            c.lps = 16;
+            c.upl = 1;
+        } else if (nu <= 128) {
+            c.lps *= 2;
+            c.upl = 2;
+        }
     } else if (nu > 64 && nu <= 128) {  // (64, 2) or (32, 4)
         if (bytes <= kCachedTableBytes) c = natural_cfg(h->p.dtype, h->p.d);
     } else if (nu > 32 && nu <= 64) {

@@ -19,24 +19,50 @@ constexpr int hogwild_min_waves() { return sizeof(TT) == 2 ? 5 : 3; }
 // wavefront takes tiles of 2^tile_shift samples from the launch's tile counter (g.tiles, zero at
 // launch) until none are left, so wavefronts that meet slow rows do not hold up a fixed share of
 // the work and the grid is only as large as what is resident.  A launch with no more tiles than
-// wavefronts has no counter (g.tiles NULL): wavefront t takes tile t.
+// wavefronts has no counter (g.tiles NULL): wavefront t takes tile t.  With g.streams, 2^q_shift
+// wavefronts share each of so many streams of 64-sample tiles (TileAt), tile t being a share of
+// stream (t mod (streams 2^q_shift)) / 2^q_shift; a workgroup takes four tiles at a time, and its
+// wavefronts keep step (sgd_tile).
 // FULL: the tile shape covers a row exactly (lanes x units == the row's units) and K == KMAX,
 // so row accesses need no bounds mask or slot test.
 template <typename TT, int LPS, int UPL, int KMAX, int ORD, bool SH, bool FULL = false>
 __global__ void __launch_bounds__(256, hogwild_min_waves<TT>()) k_hogwild(GraphDev g, unsigned long long first, unsigned long long end)
 {
     const unsigned lane = threadIdx.x & 63u;
-    const unsigned long long ntiles = ((end - first - 1) >> g.tile_shift) + 1;
+    __shared__ unsigned long long next;
+    const unsigned lap_waves = g.streams << g.q_shift;  // (a multiple of 4)
+    const unsigned long long ntiles = g.streams ? g.laps * lap_waves : ((end - first - 1) >> g.tile_shift) + 1;
     unsigned long long t = blockIdx.x * 4u + (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     while (true) {
         if (g.tiles) {
-            t = 0;
-            if (lane == 0) t = atomicAdd(g.tiles, 1ull);
+            if constexpr (sizeof(TT) == 4) {
+                if (g.streams) {
+                    if (threadIdx.x == 0) next = atomicAdd(g.tiles, 1ull) * 4u;
+                    __syncthreads();
+                    t = next + (threadIdx.x >> 6);
+                    __syncthreads();
+                }
+            }
+            if (!g.streams) {
+                t = 0;
+                if (lane == 0) t = atomicAdd(g.tiles, 1ull);
+            }
             t = ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(t >> 32)) << 32) |
                 (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(t & 0xffffffffull));
         }
         if (t >= ntiles) break;
-        sgd_tile<TT, LPS, UPL, KMAX, ORD, SH, FULL>(g, first + (t << g.tile_shift), end, g.tile_shift);
+        TileAt at{first + (t << g.tile_shift), 0, 0};
+        if (g.streams) {
+            constexpr int GS = __builtin_ctz(64 / LPS);
+            const unsigned long long lap = t / lap_waves;
+            const unsigned w = (unsigned)(t - lap * lap_waves), stream = w >> g.q_shift;
+            at.q_shift = g.q_shift;
+            at.apart = (unsigned long long)g.streams * 64u;
+            // 2^tile_shift samples a wavefront: 2^(tile_shift + q_shift) of the stream a lap
+            at.first = first + ((lap << (g.tile_shift + g.q_shift - 6)) * at.apart) + stream * 64u +
+                       ((w & ((1u << g.q_shift) - 1u)) << GS);
+        }
+        sgd_tile<TT, LPS, UPL, KMAX, ORD, SH, FULL>(g, at, end, g.tile_shift);
         if (!g.tiles) break;
     }
 }
@@ -92,30 +118,50 @@ inline int hot_heat_for(double W, double hot_rate)
     X(32, 8)           \
     X(64, 8)
 
-// The grid and the tile of one Hogwild launch over `count` samples (at least 1) and the samples
+// The grid and the tiles of one Hogwild launch over `count` samples (at least 1) and the samples
 // it keeps in flight: the configuration's grid, lowered if the graph's caps ask for fewer.
-// narrow: binary32 rows of 16 units, one per lane (kSmallTableCapShare).
 //
 // Tiles have 64 samples, one per lane of phase A; a launch too short to give every wavefront
 // such a tile takes smaller ones, down to four rounds of phase B (below that phase A, which costs
 // the same for any number of samples, is most of a tile's time).
+//
+// Teams (team: wavefronts to a stream, 1: none): four_unit_lanes says why.
 struct HogwildPlan {
-    unsigned grid = 1;
-    int tile_shift = 6;
+    unsigned grid = 1, streams = 0;
+    int tile_shift = 6, q_shift = 0;
+    unsigned long long laps = 0;
     bool counter = true;  // more tiles than wavefronts
     double in_flight = 0.0;
 };
 
 template <typename KernelT>
-inline HogwildPlan plan_launch(KernelT kern, int lps, bool narrow, const GraphDev &g, const TileCfg &c,
+inline HogwildPlan plan_launch(KernelT kern, int lps, int team, const GraphDev &g, const TileCfg &c,
                                unsigned long long count, int num_cu)
 {
     HogwildPlan p;
     const unsigned resident = resident_blocks(kern, num_cu);
     unsigned most_blocks = std::min((unsigned)num_cu * (unsigned)(c.blocks_per_cu > 0 ? c.blocks_per_cu : 8), resident);
     const double per_block = 4.0 * (64.0 / lps);
-    double most = g.max_in_flight;
-    if (narrow && std::isinf(g.resid) && g.staleness > 0.0) most = std::min(most, g.staleness * kSmallTableCapShare);
+    const double most = g.max_in_flight;
+    if (team > 1) {
+        // streams as the narrow shape has wavefronts: four of its workgroups' at a time
+        unsigned sets = std::max(1u, most_blocks / (unsigned)team);
+        if (most > 0.0) sets = std::min(sets, (unsigned)std::max(1.0, std::floor(std::min(most / (per_block * team), 1e9))));
+        const unsigned long long tiles = ((count - 1) >> 6) + 1;
+        p.streams = (unsigned)std::min<unsigned long long>(4ull * sets, tiles);
+        p.q_shift = __builtin_ctz((unsigned)team);
+        // tiles of the stream that a wavefront draws its share of at a time
+        int m = 0;
+        while (m < p.q_shift && (2ull << m) * p.streams <= tiles) ++m;
+        p.tile_shift = 6 - p.q_shift + m;
+        p.laps = (tiles - 1) / ((unsigned long long)p.streams << m) + 1;
+        if (team == 2) p.streams += p.streams & 1u;  // whole workgroups
+        const unsigned waves = p.streams << p.q_shift;
+        p.grid = waves / 4;
+        p.counter = p.laps > 1;
+        p.in_flight = (double)waves * (64 / lps);
+        return p;
+    }
     if (most > 0.0) most_blocks = std::min(most_blocks, (unsigned)std::max(1.0, std::floor(std::min(most / per_block, 1e9))));
     const int gpw_shift = 6 - __builtin_ctz((unsigned)lps);
     const int least = std::min(6, gpw_shift + 2);
@@ -131,13 +177,16 @@ inline HogwildPlan plan_launch(KernelT kern, int lps, bool narrow, const GraphDe
 // (bfloat16 tables) the hot rows move into the binary32 shadow for the launch and back
 // afterwards; without one no row is read from a shadow.
 template <typename KernelT>
-hipError_t launch_one(KernelT kern, int lps, bool narrow, const GraphDev &g, const TileCfg &c, unsigned long long first,
+hipError_t launch_one(KernelT kern, int lps, int team, const GraphDev &g, const TileCfg &c, unsigned long long first,
                       unsigned long long end, int num_cu, const ShadowCtx *sc, hipStream_t s)
 {
-    const HogwildPlan p = plan_launch(kern, lps, narrow, g, c, end - first, num_cu);
+    const HogwildPlan p = plan_launch(kern, lps, team, g, c, end - first, num_cu);
     GraphDev gl = g;
     gl.hot_heat = hot_heat_for(p.in_flight + g.resid, g.hot_rate);
     gl.tile_shift = p.tile_shift;
+    gl.streams = p.streams;
+    gl.q_shift = p.q_shift;
+    gl.laps = p.laps;
     if (sc) {
         hipError_t e = shadow_begin(*sc, gl.hot_heat, s);
         if (e != hipSuccess) return e;
@@ -153,10 +202,14 @@ hipError_t launch_one(KernelT kern, int lps, bool narrow, const GraphDev &g, con
     return e;
 }
 
+// Wavefronts to a stream of a launch: binary32 tables that fit in one L2, and more lanes a sample
+// than four units a lane need.
 template <typename TT>
-inline bool narrow_groups(const TileCfg &c)
+inline int team_waves(const GraphDev &g, const TileCfg &c)
 {
-    return sizeof(TT) == 4 && c.lps == 16 && c.upl == 1;
+    if (sizeof(TT) != 4 || !std::isinf(g.resid)) return 1;
+    const int narrow = four_unit_lanes(g.nunits);
+    return c.lps > narrow ? c.lps / narrow : 1;
 }
 
 // Samples a Hogwild launch of `count` samples would keep in flight (0: no such kernel);
@@ -164,12 +217,12 @@ inline bool narrow_groups(const TileCfg &c)
 template <typename TT, int ORD, bool SH>
 double hogwild_in_flight_sh(const GraphDev &g, const TileCfg &c, unsigned long long count, int num_cu)
 {
-    const bool nar = narrow_groups<TT>(c);
+    const int team = team_waves<TT>(g, c);
 #define LH_PLAN_H(L, C)                                                                                  \
     if (c.lps == L && c.upl == C) {                                                                      \
         if (!SH && g.K == 5 && L * C == g.nunits)                                                        \
-            return plan_launch(k_hogwild<TT, L, C, 5, ORD, false, true>, L, nar, g, c, count, num_cu).in_flight; \
-        return plan_launch(g.K <= 5 ? k_hogwild<TT, L, C, 5, ORD, SH> : k_hogwild<TT, L, C, 8, ORD, SH>, L, nar, g, c, \
+            return plan_launch(k_hogwild<TT, L, C, 5, ORD, false, true>, L, team, g, c, count, num_cu).in_flight; \
+        return plan_launch(g.K <= 5 ? k_hogwild<TT, L, C, 5, ORD, SH> : k_hogwild<TT, L, C, 8, ORD, SH>, L, team, g, c, \
                            count, num_cu).in_flight;                                                     \
     }
     LH_CFG_LIST(LH_PLAN_H)
@@ -189,13 +242,14 @@ template <typename TT, int ORD, bool SH>
 hipError_t launch_hogwild_sh(const GraphDev &g, const TileCfg &c, unsigned long long first, unsigned long long end,
                              int num_cu, const ShadowCtx *sc, hipStream_t s)
 {
-    const bool k5 = g.K <= 5, nar = narrow_groups<TT>(c);
+    const bool k5 = g.K <= 5;
+    const int team = team_waves<TT>(g, c);
 #define LH_LAUNCH_H(L, C)                                                                        \
     if (c.lps == L && c.upl == C) {                                                              \
         if (!SH && g.K == 5 && L * C == g.nunits)                                                \
-            return launch_one(k_hogwild<TT, L, C, 5, ORD, false, true>, L, nar, g, c, first, end, num_cu, sc, s); \
-        if (k5) return launch_one(k_hogwild<TT, L, C, 5, ORD, SH>, L, nar, g, c, first, end, num_cu, sc, s); \
-        return launch_one(k_hogwild<TT, L, C, 8, ORD, SH>, L, nar, g, c, first, end, num_cu, sc, s);        \
+            return launch_one(k_hogwild<TT, L, C, 5, ORD, false, true>, L, team, g, c, first, end, num_cu, sc, s); \
+        if (k5) return launch_one(k_hogwild<TT, L, C, 5, ORD, SH>, L, team, g, c, first, end, num_cu, sc, s); \
+        return launch_one(k_hogwild<TT, L, C, 8, ORD, SH>, L, team, g, c, first, end, num_cu, sc, s);        \
     }
     LH_CFG_LIST(LH_LAUNCH_H)
 #undef LH_LAUNCH_H

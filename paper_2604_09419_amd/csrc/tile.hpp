@@ -513,16 +513,34 @@ __device__ __forceinline__ void sgd_order(const GraphDev &g, int u, const int (&
     }
 }
 
-// One tile of samples [tile, min(tile + 2^tile_shift, end)), at most 64 and a multiple of the
-// groups per wavefront.  UPL units per lane.  SH: bfloat16
-// Hogwild with a binary32 shadow of the hot rows (compiled out otherwise: the shadow's
-// address choice and second-half loads cost a quarter of the kernel's speed even unused).
+// One tile of samples, lane l of the first 2^tile_shift drawing sample at.sample(l) if it lies
+// before end.  tile_shift is at most 6 and a tile a multiple of the groups per wavefront.  UPL units
+// per lane.  SH: bfloat16 Hogwild with a binary32 shadow of the hot rows (compiled out otherwise: the
+// shadow's address choice and second-half loads cost a quarter of the kernel's speed even unused).
+//
+// Team: 2^q_shift wavefronts work through one stream of 64-sample tiles together, each on a share of
+// every round.  GS: log2 of the groups per wavefront.  Without a team (q_shift 0) the tile is 64
+// consecutive samples.  first: the first sample of lane 0; apart: samples between two tiles of the
+// stream.
+struct TileAt {
+    unsigned long long first;
+    unsigned long long apart;
+    int q_shift;
+
+    template <int GS>
+    __device__ __forceinline__ unsigned long long sample(unsigned lane) const
+    {
+        const unsigned in_tile = lane & ((64u >> q_shift) - 1u);
+        return first + (lane >> (6 - q_shift)) * apart +
+               (((in_tile >> GS) << (GS + q_shift)) | (in_tile & ((1u << GS) - 1u)));
+    }
+};
+
 template <typename TT, int LPS, int UPL, int KMAX, int ORD, bool SH, bool FULL = false>
-__device__ __forceinline__ void sgd_tile(const GraphDev &g, unsigned long long tile, unsigned long long end,
-                                         int tile_shift = 6)
+__device__ __forceinline__ void sgd_tile(const GraphDev &g, const TileAt &at, unsigned long long end, int tile_shift = 6)
 {
     static_assert(LPS >= 1 && LPS <= 64 && (64 % LPS) == 0, "lanes per sample divide the wavefront");
-    constexpr int GPW = 64 / LPS;
+    constexpr int GPW = 64 / LPS, GS = __builtin_ctz(GPW);
     const int lane = threadIdx.x & 63;
     const int grp = lane / LPS, gl = lane % LPS;
     const int K = g.K;
@@ -535,7 +553,7 @@ __device__ __forceinline__ void sgd_tile(const GraphDev &g, unsigned long long t
 #pragma unroll
     for (int j = 0; j <= KMAX; ++j) my_ids[j] = 0;
     {
-        const unsigned long long s = tile + (unsigned long long)lane;
+        const unsigned long long s = at.sample<GS>((unsigned)lane);
         if (s < end && (lane >> tile_shift) == 0) {
             // One Philox block at a time, its record load issued at once, so the loads of
             // all 1 + K slots are in flight together while the blocks are not interleaved
@@ -603,12 +621,17 @@ __device__ __forceinline__ void sgd_tile(const GraphDev &g, unsigned long long t
                         }
                 }
             }
+            my_hot |= 0x80000000u;
         }
     }
 
     // ---- phase B: LPS lanes per sample ----------------------------------------
     const int rounds = (1 << tile_shift) / GPW;
     for (int r = 0; r < rounds; ++r) {
+        // a team's wavefronts take their samples of a round at the same time, as one wavefront of the
+        // narrow shape takes them all (every wavefront of the workgroup has the same rounds)
+        if constexpr (sizeof(TT) == 4 && !SH)
+            if (at.q_shift) __builtin_amdgcn_s_barrier();
         const int src = r * GPW + grp;
         const int u = sample_lane<LPS>(my_u, src);
         int ids[KMAX + 1];
@@ -620,8 +643,7 @@ __device__ __forceinline__ void sgd_tile(const GraphDev &g, unsigned long long t
         if constexpr (sizeof(TT) == 2) sr = (uint32_t)sample_lane<LPS>((int)my_sr, src);
         // every cross-lane read before lanes diverge
         const float eta = __int_as_float(sample_lane<LPS>(__float_as_int(my_eta), src));
-        const unsigned long long s = tile + (unsigned long long)src;
-        if (s >= end) continue;
+        if ((int)hot >= 0) continue;  // no sample: past the end
         const unsigned dupb = dup & 0xffffu, dupu = dup >> 16;
         // Issue the row loads of both orders before any arithmetic or store, so that up to
         // 2 (2 + K) rows per sample are in flight at once.
