@@ -621,7 +621,6 @@ __device__ __forceinline__ void sgd_tile(const GraphDev &g, const TileAt &at, un
                         }
                 }
             }
-            my_hot |= 0x80000000u;
         }
     }
 
@@ -643,7 +642,11 @@ __device__ __forceinline__ void sgd_tile(const GraphDev &g, const TileAt &at, un
         if constexpr (sizeof(TT) == 2) sr = (uint32_t)sample_lane<LPS>((int)my_sr, src);
         // every cross-lane read before lanes diverge
         const float eta = __int_as_float(sample_lane<LPS>(__float_as_int(my_eta), src));
-        if ((int)hot >= 0) continue;  // no sample: past the end
+        // (from the index, not from a flag that phase A leaves: the loads would wait for its permute)
+        unsigned long long s = at.first + (unsigned)src;
+        if constexpr (sizeof(TT) == 4 && !SH)
+            if (at.q_shift) s = at.sample<GS>((unsigned)src);
+        if (s >= end) continue;
         const unsigned dupb = dup & 0xffffu, dupu = dup >> 16;
         // Issue the row loads of both orders before any arithmetic or store, so that up to
         // 2 (2 + K) rows per sample are in flight at once.
