@@ -228,13 +228,14 @@ inline int four_unit_lanes(int nunits)
 // A launch keeps no more samples in flight than the graph's hottest row can serve: its updates are
 // atomics on the same lines, one after the other (24 ns per 256 bytes), so with p_max the
 // probability that a sample touches it, more than about latency / (p_max x that time) samples
-// only queue there, and enlarge the hot set besides.  Measured optimum over 40,000 to 2^21 nodes,
-// widths 16 to 200 and both types: p_max x samples about 32, and 48 for rows of at most 128 bytes
-// (a shorter service) and for tables beyond the Infinity Cache (a longer latency: 2^20 nodes,
-// d = 128, both orders 2.72 ns at 4,096 and 2.80 at 2,048).
-// d = 128, 150,000 nodes: 2.07 ns a sample at 1,024 in flight, 2.54 at 3,072; 300,000 nodes, both
-// orders: 3.03 at 1,536, 4.89 at 6,144.  Graphs without hubs are not limited by it.
-constexpr double kHottestInFlight = 32.0, kHottestInFlightMore = 48.0;
+// only queue there, and enlarge the hot set besides.  p_max x samples of 32, 48, 72 and 100 over
+// 40,000 to 300,000 nodes, both types, widths 32 to 200, one order and both: at 48 launches take
+// 0.98-2.0 of the speed they have without this limit and with the narrow shapes (300,000 nodes,
+// d = 128, both orders 1.62, d = 72 1.31), at 32 down to 0.7 (40,000 nodes, d = 72 3.5 and 4.9 ms), at 72
+// and above the gains fall (d = 128 1.26).  Rows of at most 64 bytes are served in less time: 120,000
+// nodes, d = 32, bfloat16, both orders 1.54 ms at 48, 1.43 at 100.  Graphs without hubs are not
+// limited by it.
+constexpr double kHottestInFlight = 48.0, kHottestInFlightNarrow = 96.0;
 // Bytes of the tables' rows that have an arc.
 inline double tables_bytes(const lh_handle *h)
 {

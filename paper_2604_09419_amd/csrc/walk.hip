@@ -71,7 +71,7 @@ struct LongRow {
 };
 
 struct WalkScratch {
-    size_t k0, w0, h0, k1, w1, h1, hist, part, cnt, rows, huge, slot_row, blk, tot, mxl, off, before, total;
+    size_t k0, w0, h0, k1, w1, h1, dx, hist, part, cnt, rows, huge, slot_row, blk, tot, mxl, off, before, total;
 };
 
 WalkScratch walk_scratch_layout(long long n, long long m)
@@ -87,6 +87,7 @@ WalkScratch walk_scratch_layout(long long n, long long m)
     L.k1 = carve(off, 4 * (size_t)E);
     L.w1 = carve(off, 4 * (size_t)E);
     L.h1 = carve(off, 4 * (size_t)E);
+    L.dx = carve(off, 8 * (size_t)E);
     L.hist = carve(off, 4 * (size_t)sort_hist_size(E));
     L.part = carve(off, 4 * (size_t)sort_part_size(E));
     L.cnt = carve(off, 3 * sizeof(unsigned long long));
@@ -707,9 +708,8 @@ static lh_status build_walk(lh_handle *h, char *persist, char *scratch, const Wa
     T.ws = ws;
     T.hs = hs;
     T.rec = w.rec;
-    // in the sort's other buffers (both payloads together hold E binary64 values)
-    T.dx = (double *)rest.p0;
-    T.idx = rest.k;
+    T.dx = (double *)(scratch + S.dx);
+    T.idx = rest.k;  // (the sort is done)
     T.blk = words(S.blk);
     T.tot = (double *)(scratch + S.tot);
     T.mxl = (double *)(scratch + S.mxl);
