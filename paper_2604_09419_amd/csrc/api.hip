@@ -44,7 +44,9 @@ GraphDev graph_dev(const lh_handle *h)
     g.staleness = g.max_in_flight = staleness_cap(h);
     if (h->p_max > 0.0) {
         const double row_bytes = h->p.d * (h->p.dtype == LH_FP32 ? 4.0 : 2.0);
-        const double F = std::max(64.0, (row_bytes <= 64.0 ? kHottestInFlightNarrow : kHottestInFlight) / h->p_max);
+        const bool wide = row_bytes >= 256.0 && h->p.dtype == LH_BF16 && tables_bytes(h) <= kCachedTableBytes;
+        const double c = row_bytes <= 64.0 ? kHottestInFlightNarrow : wide ? kHottestInFlightWide : kHottestInFlight;
+        const double F = std::max(64.0, c / h->p_max);
         if (!(g.max_in_flight > 0.0) || F < g.max_in_flight) g.max_in_flight = F;
     }
     g.resid = small_table_window(h->l2_bytes, tables_bytes(h));

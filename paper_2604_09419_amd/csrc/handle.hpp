@@ -214,8 +214,8 @@ constexpr double kCachedTableBytes = 512.0 * 1048576.0;
 // 0.3-0.5 %, whatever the samples in flight.  So 2^q_shift wavefronts share the tiles that one
 // wavefront of the narrow shape would take, each a share of every round and in step with the others
 // of its workgroup, and the samples are taken in its order.  10,000 nodes, 10^6 samples, narrow and
-// wide: d = 16 28.3 and 5.7 ms for (16, 1), d = 32 14.7 and 6.4 for (16, 2), d = 64 8.3 and 6.1 for
-// (32, 2); 3,500 nodes, 300,000 samples, d = 128 5.7 and 4.3 for (64, 2).  They end 0.4-0.9 % from
+// wide: d = 16 28.3 and 6.7 ms for (16, 1), d = 32 14.7 and 6.4 for (16, 2), d = 64 8.3 and 6.1 for
+// (32, 2); 3,500 nodes, 300,000 samples, d = 128 5.7 and 4.3 for (64, 2).  They end 0.4-0.8 % from
 // where the narrow shape ends (0.5-1.2 % with wavefronts out of step), and one unit a lane for wider
 // rows 0.6-1.4 % (d = 32 in 5.5 ms, d = 64 in 5.9).
 // Lanes per sample of the shape with four units a lane.
@@ -233,9 +233,12 @@ inline int four_unit_lanes(int nunits)
 // 0.98-2.0 of the speed they have without this limit and with the narrow shapes (300,000 nodes,
 // d = 128, both orders 1.62, d = 72 1.31), at 32 down to 0.7 (40,000 nodes, d = 72 3.5 and 4.9 ms), at 72
 // and above the gains fall (d = 128 1.26).  Rows of at most 64 bytes are served in less time: 120,000
-// nodes, d = 32, bfloat16, both orders 1.54 ms at 48, 1.43 at 100.  Graphs without hubs are not
+// nodes, d = 32, bfloat16, both orders 1.54 ms at 48, 1.43 at 100.  Bfloat16 rows of 256 bytes and
+// more, whose hot rows take an atomic per two elements, at 32 and 48: 300,000 nodes, d = 128, 0.80 and
+// 0.84 ms, 120,000 nodes 1.28 and 1.32, 2^20 nodes, both orders 12.65 and 12.82; but 48 beyond the
+// Infinity Cache, where latency is longer (2^23 nodes 11.66 and 11.48).  Graphs without hubs are not
 // limited by it.
-constexpr double kHottestInFlight = 48.0, kHottestInFlightNarrow = 96.0;
+constexpr double kHottestInFlight = 48.0, kHottestInFlightNarrow = 96.0, kHottestInFlightWide = 32.0;
 // Bytes of the tables' rows that have an arc.
 inline double tables_bytes(const lh_handle *h)
 {

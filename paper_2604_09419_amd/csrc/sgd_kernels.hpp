@@ -156,9 +156,10 @@ inline HogwildPlan plan_launch(KernelT kern, int lps, int team, const GraphDev &
         const unsigned long long tiles = ((count - 1) >> 6) + 1;
         p.streams = (unsigned)std::min<unsigned long long>(4ull * sets, tiles);
         p.q_shift = __builtin_ctz((unsigned)team);
-        // tiles of the stream that a wavefront draws its share of at a time
-        int m = 0;
-        while (m < p.q_shift && (2ull << m) * p.streams <= tiles) ++m;
+        // tiles of the stream that a wavefront draws its share of at a time: two, so that a team that
+        // lags does so by few samples (10,000 nodes, d = 16: four 5.8 ms, ending 1.6 times as far from
+        // the narrow shape as its own runs from each other; two 6.7 ms and 1.3 times; one 9.4 ms)
+        const int m = 2ull * p.streams <= tiles ? 1 : 0;
         p.tile_shift = 6 - p.q_shift + m;
         p.laps = (tiles - 1) / ((unsigned long long)p.streams << m) + 1;
         if (team == 2) p.streams += p.streams & 1u;  // whole workgroups
