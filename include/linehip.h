@@ -212,7 +212,7 @@ LH_API lh_status lh_tune(lh_handle *h, uint64_t probe, const char *cache_path);
  * run two samples per wavefront when at most a tenth of the row touches would then fall
  * on hot rows, else one (imported tables, whose rows are all hot: one); binary32 handles
  * choose by the tables' size.  A launch runs fewer workgroups than out[2] asks for where the
- * staleness cap (max_conflicts) or the atomics on the graph's hottest row allow no more. */
+ * staleness cap (max_conflicts) allows no more. */
 LH_API lh_status lh_kernel_config(const lh_handle *h, int32_t out[3]);
 
 /* Use configuration cfg (same layout as lh_kernel_config's out) for later Hogwild

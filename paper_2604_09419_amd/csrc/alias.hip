@@ -16,7 +16,6 @@
 // Every step is a single correctly rounded binary64 operation in a fixed order, so
 // the tables are bitwise reproducible.
 #include <algorithm>
-#include <cstring>
 #include <mutex>
 #include <vector>
 
@@ -287,7 +286,7 @@ __global__ void __launch_bounds__(256) k_neg_weights(const int32_t *deg, long lo
 }
 
 // Words of the build's small result block: what the host reads back in one copy.
-enum { CNT_ACTIVE = 0, CNT_HEAT = 1, CNT_STATUS = 257, CNT_PMAX = 258, CNT_WORDS = 259 };
+enum { CNT_ACTIVE = 0, CNT_HEAT = 1, CNT_STATUS = 257, CNT_WORDS = 258 };
 
 // The degrees and the result block of a build start at zero.
 __global__ void __launch_bounds__(256) k_build_zero(int32_t *deg, int32_t *indeg, long long n, unsigned long long *cnt)
@@ -299,28 +298,24 @@ __global__ void __launch_bounds__(256) k_build_zero(int32_t *deg, int32_t *indeg
 
 // Heat of node r (see common.hpp): floor(-log2 p_r), p_r = (out + in) / m + K nu_r / W_nu.
 // It only chooses between the write paths of the training kernel, so it is computed in
-// ordinary binary64 arithmetic.  cnt[CNT_PMAX] is the largest p_r (the bits of a non-negative
-// binary64 number order like the number), cnt[CNT_ACTIVE] counts the nodes with an arc, cnt[CNT_HEAT + h]
-// the nodes of heat h (a histogram in LDS per workgroup, then one atomic per bin; the grid
+// ordinary binary64 arithmetic.  cnt[CNT_ACTIVE] counts the nodes with an arc, cnt[CNT_HEAT + h] the
+// nodes of heat h (a histogram in LDS per workgroup, then one atomic per bin; the grid
 // is at most 256 workgroups, since every one of them ends with atomics on the same few words).
 __global__ void __launch_bounds__(256) k_heat(const int32_t *deg, const int32_t *indeg, const double *Wnu, long long n,
                                               long long m, int K, uint8_t *heat, unsigned long long *cnt)
 {
     __shared__ unsigned int hist[256];
     __shared__ unsigned int active;
-    __shared__ unsigned long long pmax;
     hist[threadIdx.x] = 0u;
-    if (threadIdx.x == 0) active = 0u, pmax = 0ull;
+    if (threadIdx.x == 0) active = 0u;
     __syncthreads();
     const double Wn = *Wnu;
     unsigned mine = 0u;
-    double top = 0.0;
     for (long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += (long long)gridDim.x * blockDim.x) {
         const int32_t od = deg[r], both = od + indeg[r];
         if (both > 0) ++mine;
         double p = (double)both / (double)m;
         if (Wn > 0.0) p += (double)K * neg_weight(od) / Wn;
-        if (p > top) top = p;
         int hv = 255;
         if (p > 0.0) {
             const double t = floor(-log2(p));
@@ -330,13 +325,9 @@ __global__ void __launch_bounds__(256) k_heat(const int32_t *deg, const int32_t 
         atomicAdd(&hist[hv], 1u);
     }
     if (mine) atomicAdd(&active, mine);
-    atomicMax(&pmax, (unsigned long long)__double_as_longlong(top));
     __syncthreads();
     if (hist[threadIdx.x]) atomicAdd(&cnt[CNT_HEAT + threadIdx.x], (unsigned long long)hist[threadIdx.x]);
-    if (threadIdx.x == 0) {
-        if (active) atomicAdd(&cnt[CNT_ACTIVE], (unsigned long long)active);
-        atomicMax(&cnt[CNT_PMAX], pmax);
-    }
+    if (threadIdx.x == 0 && active) atomicAdd(&cnt[CNT_ACTIVE], (unsigned long long)active);
 }
 
 __global__ void k_fill_u8(uint8_t *p, long long n, uint8_t v)
@@ -577,7 +568,6 @@ lh_status build_alias(lh_handle *h, void *scratch, size_t bytes)
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(h, e, "alias build");
     h->n_active = (long long)host[CNT_ACTIVE];
-    std::memcpy(&h->p_max, &host[CNT_PMAX], sizeof(double));
     for (int v = 0; v < 256; ++v) h->heat_count[v] = host[CNT_HEAT + v];
     if (host[CNT_STATUS] & ST_ZERO_TOTAL) {
         // with at least one arc some out-degree is positive: it is the arcs' total
@@ -634,7 +624,6 @@ lh_status import_alias(lh_handle *h, int which, const uint64_t *thr, const int32
     if (h->n > 0)
         hipLaunchKernelGGL(k_fill_u8, dim3((unsigned)LH_CDIV(h->n, 256)), dim3(256), 0, h->stream,
                            (uint8_t *)(h->ws + h->lay.nheat), h->n, (uint8_t)0);
-    h->p_max = 0.0;
     for (int v = 0; v < 256; ++v) h->heat_count[v] = 0;
     h->heat_count[0] = (unsigned long long)h->n;
     if (!h->cfg_pinned) h->cfg = auto_cfg(h);

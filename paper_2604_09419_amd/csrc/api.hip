@@ -1,5 +1,4 @@
 // C ABI of the linehip library: argument checks, handle state, stream ordering.
-#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -41,14 +40,7 @@ GraphDev graph_dev(const lh_handle *h)
     g.K = h->p.K;
     g.hot_heat = -1;
     g.hot_rate = h->p.hot_rate;
-    g.staleness = g.max_in_flight = staleness_cap(h);
-    if (h->p_max > 0.0) {
-        const double row_bytes = h->p.d * (h->p.dtype == LH_FP32 ? 4.0 : 2.0);
-        const bool wide = row_bytes >= 256.0 && h->p.dtype == LH_BF16 && tables_bytes(h) <= kCachedTableBytes;
-        const double c = row_bytes <= 64.0 ? kHottestInFlightNarrow : wide ? kHottestInFlightWide : kHottestInFlight;
-        const double F = std::max(64.0, c / h->p_max);
-        if (!(g.max_in_flight > 0.0) || F < g.max_in_flight) g.max_in_flight = F;
-    }
+    g.max_in_flight = staleness_cap(h);
     g.resid = small_table_window(h->l2_bytes, tables_bytes(h));
     ShadowCtx sc;
     const bool shadowed = shadow_ctx(h, &sc);

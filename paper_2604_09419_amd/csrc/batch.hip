@@ -355,7 +355,7 @@ static void batch_items(lh_batch *b, unsigned long long item_samples, bool dry, 
     double grid = (double)b->num_cu * b->blocks_per_cu;
     for (int i = 0; i < b->G; ++i) {
         const double phi = total ? (double)b->desc[i].limit / (double)total : 0.0;
-        const double cap = b->desc[i].g.staleness;
+        const double cap = b->desc[i].g.max_in_flight;
         if (cap > 0.0 && phi > 0.0) grid = std::min(grid, std::max(1.0, std::floor(cap / phi / per_block)));
     }
     b->grid = (unsigned)std::max(1.0, grid);

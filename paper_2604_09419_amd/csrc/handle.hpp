@@ -26,8 +26,7 @@ struct GraphDev {
     int K;
     int hot_heat;              // rows with heat <= hot_heat take atomic increments (-1: none)
     double hot_rate;           // host side: the threshold hot_heat is derived from per launch
-    double max_in_flight;      // host side: cap on samples in flight (0: none)
-    double staleness;          // host side: the part of it that is the staleness cap (0: none)
+    double max_in_flight;      // host side: the staleness cap on samples in flight (0: none)
     double resid;              // host side: extra hot window (infinite for tables that fit in one L2)
     // bfloat16 Hogwild: binary32 shadow rows of the hot rows ([cap x d] per table) and the
     // per-node slot map (slot >= 0: the row lives in the shadow for this launch).  NULL
@@ -157,7 +156,6 @@ struct lh_handle {
     void *tab[3] = {nullptr, nullptr, nullptr};
     long long n = 0, m = 0;
     long long n_active = 0;  // nodes with at least one arc (from the last alias build)
-    double p_max = 0.0;      // touch probability of the hottest row (last build; 0 after an import)
     unsigned long long heat_count[256] = {};  // nodes per heat value (last build or import)
     const int32_t *src = nullptr, *dst = nullptr;
     const float *w = nullptr;
@@ -225,20 +223,12 @@ inline int four_unit_lanes(int nunits)
     while (l < 64 && 4 * l < nunits) l *= 2;
     return l;
 }
-// A launch keeps no more samples in flight than the graph's hottest row can serve: its updates are
-// atomics on the same lines, one after the other (24 ns per 256 bytes), so with p_max the
-// probability that a sample touches it, more than about latency / (p_max x that time) samples
-// only queue there, and enlarge the hot set besides.  p_max x samples of 32, 48, 72 and 100 over
-// 40,000 to 300,000 nodes, both types, widths 32 to 200, one order and both: at 48 launches take
-// 0.98-2.0 of the speed they have without this limit and with the narrow shapes (300,000 nodes,
-// d = 128, both orders 1.62, d = 72 1.31), at 32 down to 0.7 (40,000 nodes, d = 72 3.5 and 4.9 ms), at 72
-// and above the gains fall (d = 128 1.26).  Rows of at most 64 bytes are served in less time: 120,000
-// nodes, d = 32, bfloat16, both orders 1.54 ms at 48, 1.43 at 100.  Bfloat16 rows of 256 bytes and
-// more, whose hot rows take an atomic per two elements, at 32 and 48: 300,000 nodes, d = 128, 0.80 and
-// 0.84 ms, 120,000 nodes 1.28 and 1.32, 2^20 nodes, both orders 12.65 and 12.82; but 48 beyond the
-// Infinity Cache, where latency is longer (2^23 nodes 11.66 and 11.48).  Graphs without hubs are not
-// limited by it.
-constexpr double kHottestInFlight = 48.0, kHottestInFlightNarrow = 96.0, kHottestInFlightWide = 32.0;
+// (No limit by the graph's hottest row, whose atomics a launch with many samples in flight queues for:
+// fewer samples in flight also make rows cold that had atomics, and racing stores then lose updates
+// that were kept.  2^20 nodes, d = 128, bfloat16, both orders, 2,500 in flight in place of 5,120: 12.65
+// against 12.98 ms, but U1 ended 0.0069 from where launches without the limit end, which are 0.0062
+// apart.  With the hot set kept as without the limit, over 40,000 to 2^20 nodes and fifteen widths and
+// orders, launches of 50,000 samples took 1.03, of 10^6 0.98 of their time, the worst 1.67.)
 // Bytes of the tables' rows that have an arc.
 inline double tables_bytes(const lh_handle *h)
 {
