@@ -1,5 +1,5 @@
-// Hogwild kernels over a range of sample indices, and their host launchers.  Each (dtype, orders) pair is instantiated in its own translation
-// unit so the kernel variants compile in parallel.
+// Hogwild kernels over a range of sample indices, and their host launchers.  Each (dtype, orders)
+// pair is instantiated in its own translation unit so the kernel variants compile in parallel.
 #pragma once
 
 #include <algorithm>
@@ -12,38 +12,46 @@ namespace lh {
 // Register budget of the one-graph kernel: at least 3 (binary32) or 5 (bfloat16) waves per
 // SIMD.  The bfloat16 kernel is latency bound: 5 waves (96 registers, no spills) measured
 // 2 % faster than 4 on both hub-heavy and large uniform tables, and 6 (with spills) slower.
-template <typename TT>
-constexpr int hogwild_min_waves() { return sizeof(TT) == 2 ? 5 : 3; }
+// Both orders with several samples a wavefront do not fit 96 registers: what is spilled is read back in
+// every round, and the wait for that also waits for the stores before it to be acknowledged.  With 4
+// waves for one unit a lane and 3 for more, nothing is spilled; graphs without hubs, 5 waves and so:
+// 40,000 nodes, 640,000 samples, d = 32 1.25 and 1.09 ms, d = 128 2.73 and 1.27, d = 256 7.0 and 1.93;
+// 2^20 nodes, 10^6 samples, d = 128 2.34 and 1.34 (4 waves and 3 spilled registers 1.32).
+template <typename TT, int LPS, int UPL, int ORD>
+constexpr int hogwild_min_waves()
+{
+    if (sizeof(TT) == 4) return 3;
+    return ORD == 3 && LPS < 64 ? (UPL > 1 ? 3 : 4) : 5;
+}
 
 // SH: bfloat16 tables whose hot rows live in a binary32 shadow for the launch.  Each
 // wavefront takes tiles of 2^tile_shift samples from the launch's tile counter (g.tiles, zero at
 // launch) until none are left, so wavefronts that meet slow rows do not hold up a fixed share of
 // the work and the grid is only as large as what is resident.  A launch with no more tiles than
-// wavefronts has no counter (g.tiles NULL): wavefront t takes tile t.  With g.streams, 2^q_shift
-// wavefronts share each of so many streams of 64-sample tiles (TileAt), tile t being a share of
+// wavefronts has no counter (g.tiles NULL): wavefront t takes tile t.  With g.streams (binary32),
+// 2^q_shift wavefronts share each of so many streams of 64-sample tiles (TileAt), tile t being a share of
 // stream (t mod (streams 2^q_shift)) / 2^q_shift; a workgroup takes four tiles at a time, and its
 // wavefronts keep step (sgd_tile).
 // FULL: the tile shape covers a row exactly (lanes x units == the row's units) and K == KMAX,
 // so row accesses need no bounds mask or slot test.
 template <typename TT, int LPS, int UPL, int KMAX, int ORD, bool SH, bool FULL = false>
-__global__ void __launch_bounds__(256, hogwild_min_waves<TT>()) k_hogwild(GraphDev g, unsigned long long first, unsigned long long end)
+__global__ void __launch_bounds__(256, (hogwild_min_waves<TT, LPS, UPL, ORD>())) k_hogwild(GraphDev g, unsigned long long first,
+                                                                                     unsigned long long end)
 {
     const unsigned lane = threadIdx.x & 63u;
     __shared__ unsigned long long next;
-    const unsigned lap_waves = g.streams << g.q_shift;  // (a multiple of 4)
-    const unsigned long long ntiles = g.streams ? g.laps * lap_waves : ((end - first - 1) >> g.tile_shift) + 1;
+    const unsigned streams = sizeof(TT) == 4 ? g.streams : 0u;
+    const unsigned lap_waves = streams << g.q_shift;  // (a multiple of 4)
+    const unsigned long long ntiles = streams ? g.laps * lap_waves : ((end - first - 1) >> g.tile_shift) + 1;
     unsigned long long t = blockIdx.x * 4u + (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     while (true) {
         if (g.tiles) {
-            if constexpr (sizeof(TT) == 4) {
-                if (g.streams) {
-                    if (threadIdx.x == 0) next = atomicAdd(g.tiles, 1ull) * 4u;
-                    __syncthreads();
-                    t = next + (threadIdx.x >> 6);
-                    __syncthreads();
-                }
-            }
-            if (!g.streams) {
+            if (streams) {
+                if (threadIdx.x == 0) next = atomicAdd(g.tiles, 1ull) * 4u;
+                __syncthreads();
+                t = next + (threadIdx.x >> 6);
+                __syncthreads();
+            } else {
                 t = 0;
                 if (lane == 0) t = atomicAdd(g.tiles, 1ull);
             }
@@ -52,12 +60,12 @@ __global__ void __launch_bounds__(256, hogwild_min_waves<TT>()) k_hogwild(GraphD
         }
         if (t >= ntiles) break;
         TileAt at{first + (t << g.tile_shift), 0, 0};
-        if (g.streams) {
+        if (streams) {
             constexpr int GS = __builtin_ctz(64 / LPS);
             const unsigned long long lap = t / lap_waves;
             const unsigned w = (unsigned)(t - lap * lap_waves), stream = w >> g.q_shift;
             at.q_shift = g.q_shift;
-            at.apart = (unsigned long long)g.streams * 64u;
+            at.apart = (unsigned long long)streams * 64u;
             // 2^tile_shift samples a wavefront: 2^(tile_shift + q_shift) of the stream a lap
             at.first = first + ((lap << (g.tile_shift + g.q_shift - 6)) * at.apart) + stream * 64u +
                        ((w & ((1u << g.q_shift) - 1u)) << GS);

@@ -1,0 +1,54 @@
+"""The both-order bfloat16 Hogwild kernels with several samples a wavefront keep their registers: a
+register that the sampling loop spills costs a scratch load there, and its wait also waits for the
+acknowledgements of the stores before it.  Reads the metadata of the code objects in the built library."""
+import re
+import struct
+
+import msgpack
+import pytest
+
+from paper_2604_09419_amd import build as hipbuild
+
+
+def _code_objects(data):
+    magic = b"__CLANG_OFFLOAD_BUNDLE__"
+    at = data.find(magic)
+    while at >= 0:
+        (n,) = struct.unpack_from("<Q", data, at + 24)
+        p = at + 32
+        for _ in range(n):
+            off, size, length = struct.unpack_from("<QQQ", data, p)
+            triple = data[p + 24:p + 24 + length]
+            p += 24 + length
+            if triple.endswith(b"gfx950") and size:
+                yield data[at + off:at + off + size]
+        at = data.find(magic, at + 24)
+
+
+def _kernels(elf):
+    """The kernels' records of an AMDGPU code object's metadata note."""
+    shoff, = struct.unpack_from("<Q", elf, 0x28)
+    shentsize, shnum = struct.unpack_from("<HH", elf, 0x3A)
+    for i in range(shnum):
+        _, kind, _, _, off, size = struct.unpack_from("<IIQQQQ", elf, shoff + i * shentsize)
+        if kind != 7:  # SHT_NOTE
+            continue
+        namesz, descsz, note = struct.unpack_from("<III", elf, off)
+        if note == 32:  # NT_AMDGPU_METADATA
+            desc = off + 12 + (namesz + 3) // 4 * 4
+            yield from msgpack.unpackb(elf[desc:desc + descsz])["amdhsa.kernels"]
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    with open(hipbuild.SO, "rb") as f:
+        data = f.read()
+    return {k[".name"]: k for c in _code_objects(data) for k in _kernels(c)}
+
+
+@pytest.mark.parametrize("lanes,units", [(16, 1), (32, 1), (16, 2), (32, 2)])
+def test_both_orders_bfloat16_kernels_spill_nothing(kernels, lanes, units):
+    found = [k for name, k in kernels.items()
+             if re.search(rf"k_hogwildItLi{lanes}ELi{units}ELi5ELi3ELb0ELb[01]E", name)]
+    assert len(found) == 2
+    assert [k[".vgpr_spill_count"] for k in found] == [0, 0]
