@@ -89,7 +89,11 @@ typedef struct {
     double max_conflicts; /* HOGWILD: the launch keeps F samples in flight with
                            F (2 + K) / n_active <= max_conflicts, n_active = nodes with an
                            arc, so that a row of average traffic has at most this many
-                           concurrent writers (staleness bound).  <= 0: no cap.          */
+                           concurrent writers (staleness bound).  A launch runs at least
+                           one workgroup, whatever the cap: four wavefronts of 64 / lanes
+                           samples (lh_kernel_config; tables of binary32 that fit in one
+                           XCD's L2 and no pinned configuration: lanes = the least power of
+                           two >= max(2, d / 4)).  <= 0: no cap.                         */
     int32_t hot_shadow; /* HOGWILD with LH_BF16 tables: 0 = hot rows take packed bfloat16
                            atomic adds of SR(row + increment) - row, SR the stochastic
                            rounding a cold row is stored with (without a concurrent write

@@ -48,6 +48,7 @@ GraphDev graph_dev(const lh_handle *h)
     g.slot = shadowed ? sc.slot : nullptr;
     g.tiles = h->ws ? (unsigned long long *)(h->ws + h->lay.tiles) : nullptr;
     g.tile_shift = 6;
+    g.teams = !h->cfg_pinned;
     g.streams = 0;
     g.q_shift = 0;
     g.laps = 0;

@@ -38,7 +38,9 @@ struct GraphDev {
     unsigned long long *tiles;
     int tile_shift;
     // Launches of wavefront teams (four_unit_lanes): streams of tiles (0: no teams), log2 of a team's
-    // wavefronts, and laps, in each of which every team takes tiles of its stream.
+    // wavefronts, and laps, in each of which every team takes tiles of its stream.  teams, host side:
+    // the launch may take them (a pinned configuration runs as it was pinned).
+    bool teams;
     unsigned streams;
     int q_shift;
     unsigned long long laps;
@@ -215,7 +217,9 @@ constexpr double kCachedTableBytes = 512.0 * 1048576.0;
 // wide: d = 16 28.3 and 6.7 ms for (16, 1), d = 32 14.7 and 6.4 for (16, 2), d = 64 8.3 and 6.1 for
 // (32, 2); 3,500 nodes, 300,000 samples, d = 128 5.7 and 4.3 for (64, 2).  They end 0.4-0.8 % from
 // where the narrow shape ends (0.5-1.2 % with wavefronts out of step), and one unit a lane for wider
-// rows 0.6-1.4 % (d = 32 in 5.5 ms, d = 64 in 5.9).
+// rows 0.6-1.4 % (d = 32 in 5.5 ms, d = 64 in 5.9).  Only for the shapes that auto_cfg chooses: a team
+// of 16 that a pinned (64, 1) at d = 16 would need draws 8 samples at a time (3,000 nodes, 48,000
+// samples 1.82 ms as teams, 0.81 as pinned), and a workgroup of it holds 4 samples, four streams 64.
 // Lanes per sample of the shape with four units a lane.
 inline int four_unit_lanes(int nunits)
 {

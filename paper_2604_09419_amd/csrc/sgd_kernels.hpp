@@ -218,12 +218,12 @@ hipError_t launch_one(KernelT kern, int lps, int team, const GraphDev &g, const 
     return e;
 }
 
-// Wavefronts to a stream of a launch: binary32 tables that fit in one L2, and more lanes a sample
-// than four units a lane need.
+// Wavefronts to a stream of a launch (1: no teams): binary32 tables that fit in one L2, a shape that
+// was not pinned, and more lanes a sample than four units a lane need.
 template <typename TT>
 inline int team_waves(const GraphDev &g, const TileCfg &c)
 {
-    if (sizeof(TT) != 4 || !std::isinf(g.resid)) return 1;
+    if (sizeof(TT) != 4 || !g.teams || !std::isinf(g.resid)) return 1;
     const int narrow = four_unit_lanes(g.nunits);
     return c.lps > narrow ? c.lps / narrow : 1;
 }
