@@ -196,12 +196,17 @@ double hot_touch_share(const unsigned long long *heat_count, int hot_heat, int K
 // Samples in flight of a Hogwild launch of `count` samples in configuration c.
 double hogwild_in_flight(const GraphDev &g, int dtype, int orders, const TileCfg &c, unsigned long long count,
                          int num_cu);
-// Largest hot share at which a bfloat16 handle runs two samples per wavefront.
-constexpr double kTwoPerWaveMaxHotShare = 0.1;
+// Largest hot share at which a handle runs two samples per wavefront (binary32: rows of 65 to 128 units
+// in large tables, below).
+constexpr double kTwoPerWaveMaxHotShare = 0.1, kTwoPerWaveMaxHotShareF32 = 0.2;
 // Binary32 shapes (K = 5, second order, ns a sample on R-MAT graphs at the launch's own samples in
 // flight).  Rows of 65 to 128 units: (32, 4) up to this size of tables, which the Infinity Cache
 // still serves for the most part (300,000 nodes, 307 MB: 1.67 against 1.82), above it (64, 2),
-// whose cold rows take the streaming stores (2^20 nodes, 1.07 GB: 1.50 against 1.56).  Rows of
+// whose cold rows take the streaming stores (2^20 nodes, 1.07 GB: 1.50 against 1.56), unless no more
+// than kTwoPerWaveMaxHotShareF32 of the touches fall on hot rows: then (32, 4) with its eight
+// workgroups per CU (2^20 nodes, uniform arcs and R-MAT ones mixed: share 0 1.29 against 1.60, 0.14
+// 1.40 and 1.54, 0.19 1.54 and 1.48, 0.31 1.64 and 1.50; both orders 2.61 and 3.12, 2.58 and 2.95, 2.70
+// and 2.76, 2.82 and 2.78).  Rows of
 // 33 to 64 units: (32, 2) (150,000 nodes: 1.76 against 1.78 for (64, 1) and 2.37 for (16, 4)).
 constexpr double kCachedTableBytes = 512.0 * 1048576.0;
 // Tables that fit in one L2 have every row updated atomically: no update is lost, and what a run

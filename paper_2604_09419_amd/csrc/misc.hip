@@ -91,7 +91,7 @@ static int next_pow2(int x)
 
 static int units_per_row(int dtype, int d) { return dtype == LH_FP32 ? d : d / 2; }
 
-// SNAPSHOT's configuration: four units (16 bytes) per lane, lanes = next power of two.
+// Four units (16 bytes) per lane, lanes = next power of two.
 TileCfg natural_cfg(int dtype, int d)
 {
     const int nu = units_per_row(dtype, d);
@@ -149,7 +149,15 @@ double hogwild_in_flight(const GraphDev &g, int dtype, int orders, const TileCfg
     return hogwild_in_flight_t<uint16_t, 3>(g, c, count, num_cu);
 }
 
-// Binary32 shapes, by the tables' size (see handle.hpp).
+// Share of the row touches that fall on hot rows in a launch of configuration c (1: no such kernel).
+static double hot_share(const lh_handle *h, const TileCfg &c)
+{
+    const GraphDev g = graph_dev(h);
+    const double F = hogwild_in_flight(g, h->p.dtype, h->p.orders, c, h->p.total_samples, h->num_cu);
+    return F > 0.0 ? hot_touch_share(h->heat_count, hot_heat_for(F + g.resid, g.hot_rate), h->p.K) : 1.0;
+}
+
+// Binary32 shapes, by the tables' size and the hub rows' share of the touches (see handle.hpp).
 static TileCfg auto_cfg_f32(const lh_handle *h, const TileCfg &wide)
 {
     const int nu = h->p.d;
@@ -165,7 +173,8 @@ static TileCfg auto_cfg_f32(const lh_handle *h, const TileCfg &wide)
             c.upl = 2;
         }
     } else if (nu > 64 && nu <= 128) {  // (64, 2) or (32, 4)
-        if (bytes <= kCachedTableBytes) c = natural_cfg(h->p.dtype, h->p.d);
+        const TileCfg two = natural_cfg(h->p.dtype, h->p.d);
+        if (bytes <= kCachedTableBytes || hot_share(h, two) <= kTwoPerWaveMaxHotShareF32) c = two;
     } else if (nu > 32 && nu <= 64) {
         c.lps = 32;
         c.upl = 2;
@@ -183,11 +192,7 @@ TileCfg auto_cfg(const lh_handle *h)
     two.lps = one.lps / 2;
     two.upl = one.upl * 2;
     if (!cfg_supported(h->p.dtype, h->p.d, two)) return one;
-    const GraphDev g = graph_dev(h);
-    const double F = hogwild_in_flight(g, h->p.dtype, h->p.orders, two, h->p.total_samples, h->num_cu);
-    if (!(F > 0.0)) return one;
-    const int hot = hot_heat_for(F + g.resid, g.hot_rate);
-    return hot_touch_share(h->heat_count, hot, h->p.K) <= kTwoPerWaveMaxHotShare ? two : one;
+    return hot_share(h, two) <= kTwoPerWaveMaxHotShare ? two : one;
 }
 
 bool cfg_supported(int dtype, int d, const TileCfg &c)
