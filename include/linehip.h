@@ -215,7 +215,9 @@ LH_API lh_status lh_tune(lh_handle *h, uint64_t probe, const char *cache_path);
  * one, lh_build_alias and lh_import_alias choose it from the degrees: bfloat16 handles
  * run two samples per wavefront when at most a tenth of the row touches would then fall
  * on hot rows, else one (imported tables, whose rows are all hot: one); binary32 handles
- * choose by the tables' size.  A launch runs fewer workgroups than out[2] asks for where the
+ * choose by the tables' size and the hub rows' share of the touches (where they run one
+ * sample per wavefront in rows of 65 to 128 elements, launches of fewer than 2^17 samples
+ * run two).  A launch runs fewer workgroups than out[2] asks for where the
  * staleness cap (max_conflicts) allows no more. */
 LH_API lh_status lh_kernel_config(const lh_handle *h, int32_t out[3]);
 

@@ -336,8 +336,8 @@ lh_status lh_train_steps(lh_handle *h, uint64_t first, uint64_t count)
             gd.pairs = pairs;
             gd.pairs_first = pf;
             gd.pool_n = pairs ? h->walk.pool : 0;
-            hipError_t le = launch_hogwild(gd, h->p.dtype, h->p.orders, h->cfg, sf, sf + sc, h->num_cu,
-                                           shadowed ? &shc : nullptr, h->stream);
+            hipError_t le = launch_hogwild(gd, h->p.dtype, h->p.orders, launch_cfg(h, sc), sf, sf + sc,
+                                           h->num_cu, shadowed ? &shc : nullptr, h->stream);
             return le == hipSuccess ? LH_OK : hip_fail(h, le, "hogwild launch");
         }
         return train_snapshot(h, sf, sc, pairs, pf);

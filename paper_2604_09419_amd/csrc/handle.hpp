@@ -257,6 +257,13 @@ inline double staleness_cap(const lh_handle *h)
 // in large tables, but they also enlarge the hot set, whose atomics cost more than that
 // gain where hub rows take a large share of the touches.  Binary32: as above.
 TileCfg auto_cfg(const lh_handle *h);
+// The configuration of a launch of `count` samples: the handle's, but where auto_cfg chose (64, 2) for
+// binary32 a launch of fewer than kShortLaunch samples takes (32, 4).  With fewer tiles than wavefronts a
+// sample a wavefront leaves half as many in flight (2^20 nodes, d = 128, hub rows: 40,000 samples 112
+// against 71 us, 64,000 127 and 94, 130,000 215 and 209; both orders 158 and 129, 202 and 193, 385 and
+// 405).
+constexpr unsigned long long kShortLaunch = 1ull << 17;
+TileCfg launch_cfg(const lh_handle *h, unsigned long long count);
 bool cfg_supported(int dtype, int d, const TileCfg &c);
 hipError_t launch_hogwild(const GraphDev &g, int dtype, int orders, const TileCfg &c,
                           unsigned long long first, unsigned long long end, int num_cu,

@@ -195,6 +195,13 @@ TileCfg auto_cfg(const lh_handle *h)
     return hot_share(h, two) <= kTwoPerWaveMaxHotShare ? two : one;
 }
 
+TileCfg launch_cfg(const lh_handle *h, unsigned long long count)
+{
+    const bool one = !h->cfg_pinned && h->p.dtype == LH_FP32 && h->cfg.lps == 64 && h->cfg.upl == 2 &&
+                     tables_bytes(h) > kCachedTableBytes;
+    return one && count < kShortLaunch ? natural_cfg(h->p.dtype, h->p.d) : h->cfg;
+}
+
 bool cfg_supported(int dtype, int d, const TileCfg &c)
 {
     bool listed = false;
