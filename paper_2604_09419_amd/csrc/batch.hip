@@ -262,13 +262,13 @@ __global__ void __launch_bounds__(256, (batch_min_waves<TT, SH>())) k_batch(Batc
         const bool kfull = g.K == KMAX;
         if (kfull && g.nunits == Cfg::LS * Cfg::US) {
             for (unsigned long long t = s0; t < s1; t += 64)
-                sgd_tile<TT, Cfg::LS, Cfg::US, KMAX, 2, SH, true>(g, TileAt{t, 0, 0}, s1);
+                sgd_tile<TT, Cfg::LS, Cfg::US, KMAX, 2, SH, true>(g, TileAt{t, samples_left(s1 - t), 0, 0});
         } else if (kfull && g.nunits == Cfg::LL * Cfg::UL) {
             for (unsigned long long t = s0; t < s1; t += 64)
-                sgd_tile<TT, Cfg::LL, Cfg::UL, KMAX, 2, SH, true>(g, TileAt{t, 0, 0}, s1);
+                sgd_tile<TT, Cfg::LL, Cfg::UL, KMAX, 2, SH, true>(g, TileAt{t, samples_left(s1 - t), 0, 0});
         } else {
             for (unsigned long long t = s0; t < s1; t += 64)
-                sgd_tile<TT, Cfg::LL, Cfg::UL, KMAX, 2, SH>(g, TileAt{t, 0, 0}, s1);
+                sgd_tile<TT, Cfg::LL, Cfg::UL, KMAX, 2, SH>(g, TileAt{t, samples_left(s1 - t), 0, 0});
         }
         if (lane == 0 && s1 > s0) atomicAdd(&a.done[lo], s1 - s0);
     }

@@ -59,18 +59,21 @@ __global__ void __launch_bounds__(256, (hogwild_min_waves<TT, LPS, UPL, ORD>()))
                 (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(t & 0xffffffffull));
         }
         if (t >= ntiles) break;
-        TileAt at{first + (t << g.tile_shift), 0, 0};
+        unsigned long long before = t << g.tile_shift;  // samples of the launch before the tile
+        TileAt at{0, 0, 0, 0};
         if (streams) {
             constexpr int GS = __builtin_ctz(64 / LPS);
             const unsigned long long lap = t / lap_waves;
             const unsigned w = (unsigned)(t - lap * lap_waves), stream = w >> g.q_shift;
             at.q_shift = g.q_shift;
-            at.apart = (unsigned long long)streams * 64u;
+            at.apart = streams * 64u;
             // 2^tile_shift samples a wavefront: 2^(tile_shift + q_shift) of the stream a lap
-            at.first = first + ((lap << (g.tile_shift + g.q_shift - 6)) * at.apart) + stream * 64u +
-                       ((w & ((1u << g.q_shift) - 1u)) << GS);
+            before = ((lap << (g.tile_shift + g.q_shift - 6)) * at.apart) + stream * 64u +
+                     ((w & ((1u << g.q_shift) - 1u)) << GS);
         }
-        sgd_tile<TT, LPS, UPL, KMAX, ORD, SH, FULL>(g, at, end, g.tile_shift);
+        at.first = first + before;
+        at.left = before < end - first ? samples_left(end - first - before) : 0u;
+        sgd_tile<TT, LPS, UPL, KMAX, ORD, SH, FULL>(g, at, g.tile_shift);
         if (!g.tiles) break;
     }
 }

@@ -12,7 +12,7 @@
 //            group holds units gl, gl + LPS, gl + 2 LPS, ... so every load, store and
 //            atomic instruction of the group covers LPS consecutive units.  The 1 + K
 //            dot products are reduced across the group with DPP, and the updates of
-//            Algorithm 1 / Eqs. (2)-(3) are written back .
+//            Algorithm 1 / Eqs. (2)-(3) are written back.
 //
 // HOGWILD write-back: a cold row is stored (row as loaded plus the sample's increment;
 // no locks) with a system-scope store (binary32 rows of a one-sample wavefront: a
@@ -513,31 +513,35 @@ __device__ __forceinline__ void sgd_order(const GraphDev &g, int u, const int (&
     }
 }
 
-// One tile of samples, lane l of the first 2^tile_shift drawing sample at.sample(l) if it lies
-// before end.  tile_shift is at most 6 and a tile a multiple of the groups per wavefront.  UPL units
-// per lane.  SH: bfloat16 Hogwild with a binary32 shadow of the hot rows (compiled out otherwise: the
+// One tile of samples, lane l of the first 2^tile_shift drawing sample at.first + at.offset(l) if
+// fewer than at.left lie before it.  tile_shift is at most 6 and a tile a multiple of the groups per
+// wavefront.  UPL units per lane.  SH: bfloat16 Hogwild with a binary32 shadow of the hot rows (compiled out otherwise: the
 // shadow's address choice and second-half loads cost a quarter of the kernel's speed even unused).
 //
 // Team: 2^q_shift wavefronts work through one stream of 64-sample tiles together, each on a share of
 // every round.  GS: log2 of the groups per wavefront.  Without a team (q_shift 0) the tile is 64
-// consecutive samples.  first: the first sample of lane 0; apart: samples between two tiles of the
-// stream.
+// consecutive samples.  first: the first sample of lane 0; left: samples of the launch from there on
+// (2^32 - 1: that many or more); apart: samples between two tiles of the stream.  Offsets are compared
+// with what is left, not samples with the end: a tile may reach past sample 2^64 - 1.
 struct TileAt {
     unsigned long long first;
-    unsigned long long apart;
+    unsigned left;
+    unsigned apart;
     int q_shift;
 
     template <int GS>
-    __device__ __forceinline__ unsigned long long sample(unsigned lane) const
+    __device__ __forceinline__ unsigned offset(unsigned lane) const
     {
         const unsigned in_tile = lane & ((64u >> q_shift) - 1u);
-        return first + (lane >> (6 - q_shift)) * apart +
+        return (lane >> (6 - q_shift)) * apart +
                (((in_tile >> GS) << (GS + q_shift)) | (in_tile & ((1u << GS) - 1u)));
     }
 };
 
+__device__ __forceinline__ unsigned samples_left(unsigned long long n) { return n < 0xffffffffull ? (unsigned)n : 0xffffffffu; }
+
 template <typename TT, int LPS, int UPL, int KMAX, int ORD, bool SH, bool FULL = false>
-__device__ __forceinline__ void sgd_tile(const GraphDev &g, const TileAt &at, unsigned long long end, int tile_shift = 6)
+__device__ __forceinline__ void sgd_tile(const GraphDev &g, const TileAt &at, int tile_shift = 6)
 {
     static_assert(LPS >= 1 && LPS <= 64 && (64 % LPS) == 0, "lanes per sample divide the wavefront");
     constexpr int GPW = 64 / LPS, GS = __builtin_ctz(GPW);
@@ -553,8 +557,9 @@ __device__ __forceinline__ void sgd_tile(const GraphDev &g, const TileAt &at, un
 #pragma unroll
     for (int j = 0; j <= KMAX; ++j) my_ids[j] = 0;
     {
-        const unsigned long long s = at.sample<GS>((unsigned)lane);
-        if (s < end && (lane >> tile_shift) == 0) {
+        const unsigned offset = at.offset<GS>((unsigned)lane);
+        if (offset < at.left && (lane >> tile_shift) == 0) {
+            const unsigned long long s = at.first + offset;
             // One Philox block at a time, its record load issued at once, so the loads of
             // all 1 + K slots are in flight together while the blocks are not interleaved
             // (which would hold 1 + K blocks of state in registers).
@@ -643,10 +648,10 @@ __device__ __forceinline__ void sgd_tile(const GraphDev &g, const TileAt &at, un
         // every cross-lane read before lanes diverge
         const float eta = __int_as_float(sample_lane<LPS>(__float_as_int(my_eta), src));
         // (from the index, not from a flag that phase A leaves: the loads would wait for its permute)
-        unsigned long long s = at.first + (unsigned)src;
+        unsigned offset = (unsigned)src;
         if constexpr (sizeof(TT) == 4 && !SH)
-            if (at.q_shift) s = at.sample<GS>((unsigned)src);
-        if (s >= end) continue;
+            if (at.q_shift) offset = at.offset<GS>((unsigned)src);
+        if (offset >= at.left) continue;
         const unsigned dupb = dup & 0xffffu, dupu = dup >> 16;
         // Issue the row loads of both orders before any arithmetic or store, so that up to
         // 2 (2 + K) rows per sample are in flight at once.
