@@ -66,11 +66,21 @@ struct u64x4 {
     unsigned long long x, y, z, w;
 };
 
-// The 128-bit product of two 64-bit words, by four 32-bit multiply-adds (__umul64hi and a plain
-// product for the low word take three multiplications more: 341 instructions a block, 272 so).
+// The 128-bit product of two 64-bit words, by four 32-bit multiply-adds.  LEAN: by __umul64hi and a
+// plain product for the low word, which takes three multiplications more (a block of Philox has 341
+// instructions in place of 272) but up to 14 registers fewer.  The bfloat16 training kernels take it: their
+// samples in flight, and with them their hot rows, follow from the wavefronts that the registers allow
+// (64 lanes a sample, second order, K = 5: 74 registers and six per SIMD, or 87 and five, which turns half
+// of the atomic rows into racing ones), and their drawing is hidden.
+template <bool LEAN>
 __device__ __forceinline__ void mul_wide(unsigned long long a, unsigned long long b, unsigned long long &hi,
                                          unsigned long long &lo)
 {
+    if (LEAN) {
+        hi = __umul64hi(a, b);
+        lo = a * b;
+        return;
+    }
     const uint32_t al = (uint32_t)a, ah = (uint32_t)(a >> 32), bl = (uint32_t)b, bh = (uint32_t)(b >> 32);
     const unsigned long long p = (unsigned long long)al * bl;
     const unsigned long long q = (unsigned long long)ah * bl + (p >> 32);
@@ -79,6 +89,7 @@ __device__ __forceinline__ void mul_wide(unsigned long long a, unsigned long lon
     lo = (r << 32) | (uint32_t)p;
 }
 
+template <bool LEAN = false>
 __device__ __forceinline__ u64x4 philox4x64_10(unsigned long long k0, unsigned long long k1,
                                                unsigned long long c0, unsigned long long c1,
                                                unsigned long long c2, unsigned long long c3)
@@ -92,8 +103,8 @@ __device__ __forceinline__ u64x4 philox4x64_10(unsigned long long k0, unsigned l
             k1 += W1;
         }
         unsigned long long hi0, lo0, hi1, lo1;
-        mul_wide(M0, c0, hi0, lo0);
-        mul_wide(M1, c2, hi1, lo1);
+        mul_wide<LEAN>(M0, c0, hi0, lo0);
+        mul_wide<LEAN>(M1, c2, hi1, lo1);
         unsigned long long n0 = hi1 ^ c1 ^ k0;
         unsigned long long n2 = hi0 ^ c3 ^ k1;
         c0 = n0;

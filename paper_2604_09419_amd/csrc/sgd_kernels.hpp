@@ -21,6 +21,7 @@ template <typename TT, int LPS, int UPL, int ORD>
 constexpr int hogwild_min_waves()
 {
     if (sizeof(TT) == 4) return 3;
+    if (ORD == 1 && LPS == 64 && UPL <= 2) return 6;  // (80 registers suffice, and the hot set stays)
     return ORD == 3 && LPS < 64 ? (UPL > 1 ? 3 : 4) : 5;
 }
 

@@ -54,9 +54,10 @@ struct SlotDraw {
     unsigned long long x2;     // a spare word of the block (seeds of the rounding bits)
 };
 
+template <bool LEAN = false>
 __device__ __forceinline__ SlotDraw draw_slot(const GraphDev &g, unsigned long long s, int j, long long N)
 {
-    const u64x4 x = philox4x64_10(g.seed, g.key1, s, (unsigned long long)j, 0ull, 0ull);
+    const u64x4 x = philox4x64_10<LEAN>(g.seed, g.key1, s, (unsigned long long)j, 0ull, 0ull);
     return SlotDraw{draw_column(x.x, N), x.y, x.z};
 }
 
@@ -563,7 +564,8 @@ __device__ __forceinline__ void sgd_tile(const GraphDev &g, const TileAt &at, in
             // One Philox block at a time, its record load issued at once, so the loads of
             // all 1 + K slots are in flight together while the blocks are not interleaved
             // (which would hold 1 + K blocks of state in registers).
-            const SlotDraw de = draw_slot(g, s, 0, slot0_columns(g));
+            constexpr bool LEAN = sizeof(TT) == 2;
+            const SlotDraw de = draw_slot<LEAN>(g, s, 0, slot0_columns(g));
             uint4 r0, r1;
             load_pair_rec<sizeof(TT) == 2>(g, s, de.col, de.x1, r0, r1);
             my_sr = (uint32_t)de.x2;
@@ -573,7 +575,7 @@ __device__ __forceinline__ void sgd_tile(const GraphDev &g, const TileAt &at, in
 #pragma unroll
             for (int j = 0; j < KMAX; ++j) {
                 if (j < K) {
-                    dn[j] = draw_slot(g, s, j + 1, g.n);
+                    dn[j] = draw_slot<LEAN>(g, s, j + 1, g.n);
                     nr[j] = *reinterpret_cast<const uint4 *>(g.nrec + dn[j].col);
                 }
                 __builtin_amdgcn_sched_barrier(0);
