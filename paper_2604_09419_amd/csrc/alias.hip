@@ -340,7 +340,7 @@ struct RecOut {
     EdgeRec *erec;  // edge table, or
     NegRec *nrec;   // negative table
     const int32_t *src, *dst;
-    const uint8_t *heat;  // per node; NULL: every node 255 (never hot)
+    const uint8_t *heat;  // per node; NULL: every node 0 (always hot)
 };
 
 // Without a heat array (imported alias tables carry no degrees) every row is taken as hot:
@@ -662,7 +662,7 @@ extern "C" lh_status lh_build_alias_noalloc(lh_handle *h)
     if (!h) return LH_ERR_INVALID_ARG;
     if (!h->graph_set) return lh::fail(h, LH_ERR_NOT_BUILT, "lh_set_graph first");
     if (h->m < 1) return lh::fail(h, LH_ERR_ZERO_WEIGHT, "the graph has no arcs");
-    // The documented limits; scratch_layout(2^21, 2^21) is 64.03 MiB, within the array.
+    // The documented limits; scratch_layout(2^21, 2^21) is 64.15 MiB, within the array.
     const lh::ScratchLayout L = lh::scratch_layout(h->n, h->m);
     if (h->n > lh::kNoAllocMaxItems || h->m > lh::kNoAllocMaxItems || L.total > lh::kNoAllocScratchBytes)
         return lh::fail(h, LH_ERR_INVALID_ARG,

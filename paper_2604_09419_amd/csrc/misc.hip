@@ -74,7 +74,8 @@ ScratchLayout scratch_layout(long long n, long long m)
     L.deg = carve(off, 4 * (size_t)(n > 0 ? n : 1));
     L.indeg = carve(off, 4 * (size_t)(n > 0 ? n : 1));
     L.cnt = carve(off, 8 * 258);
-    // (never below the 24 bytes per item that the size has always been)
+    // (24 bytes per item is the least that callers have been told, whatever the build needs: 12 for an
+    // arc when the nodes are few)
     L.total = std::max(off, lh_align_up(24 * (size_t)std::max(std::max(n, m), 1ll), 256));
     return L;
 }

@@ -131,17 +131,16 @@ inline int hot_heat_for(double W, double hot_rate)
     X(64, 8)
 
 // The grid and the tiles of one Hogwild launch over `count` samples (at least 1) and the samples
-// it keeps in flight: the configuration's grid, lowered if the graph's caps ask for fewer.
+// it keeps in flight: the configuration's grid, lowered if the staleness cap asks for fewer.
 //
-// Tiles have 64 samples, one per lane of phase A; a launch of fewer than kTilesWanted such tiles
-// takes smaller ones, down to four rounds of phase B (below that phase A, which costs the same for
-// any number of samples, is most of a tile's time).
+// Tiles have 64 samples, one per lane of phase A; a launch of fewer than kTilesWanted such tiles (two
+// wavefronts to a compute unit) takes smaller ones, down to four rounds of phase B (below that phase A,
+// which costs the same for any number of samples, is most of a tile's time).  Smaller tiles up to every
+// wavefront that may be in flight pay for phase A more often and meet more hot rows: 300,000 nodes,
+// d = 128, bfloat16, 65,536 samples 109 us with 1,024 tiles of 64, 146 with 4,096 of 16; at 8,192
+// samples 512 tiles of 16 take 31 us, 128 of 64 80, and 256 of 32 45.
 //
 // Teams (team: wavefronts to a stream, 1: none): four_unit_lanes says why.
-// Two wavefronts to a compute unit.  Smaller tiles up to every wavefront that may be in flight pay for
-// phase A more often and meet more hot rows: 300,000 nodes, d = 128, bfloat16, 65,536 samples 109 us
-// with 1,024 tiles of 64, 146 with 4,096 of 16; at 8,192 samples 512 tiles of 16 take 31 us, 128 of 64
-// 80, and 256 of 32 45.
 constexpr unsigned kTilesWanted = 512;
 
 struct HogwildPlan {

@@ -272,6 +272,7 @@ __global__ void __launch_bounds__(256) k_snap_apply(GraphDev g, const uint32_t *
 namespace {
 
 struct SnapBatch {
+    int orders;
     unsigned long long first, count, index;
     long long entries;
     const uint32_t *drawn, *keys, *vals;  // the tuples' keys in order of emission, and sorted
@@ -279,18 +280,18 @@ struct SnapBatch {
 };
 
 template <typename TT, int G, int V>
-void launch_contrib(const GraphDev &g, int orders, const SnapBatch &b, hipStream_t s)
+void launch_contrib(const GraphDev &g, const SnapBatch &b, hipStream_t s)
 {
-    const unsigned long long groups = b.count * (orders == LH_ORDER12 ? 2 : 1);
+    const unsigned long long groups = b.count * (b.orders == LH_ORDER12 ? 2 : 1);
     const dim3 grid((unsigned)LH_CDIV(groups, 256 / G)), blk(256);
     if (g.K <= 5)
-        hipLaunchKernelGGL((k_snap_contrib<TT, G, V, 5>), grid, blk, 0, s, g, orders, b.first, b.count, b.drawn, b.contrib);
+        hipLaunchKernelGGL((k_snap_contrib<TT, G, V, 5>), grid, blk, 0, s, g, b.orders, b.first, b.count, b.drawn, b.contrib);
     else
-        hipLaunchKernelGGL((k_snap_contrib<TT, G, V, 8>), grid, blk, 0, s, g, orders, b.first, b.count, b.drawn, b.contrib);
+        hipLaunchKernelGGL((k_snap_contrib<TT, G, V, 8>), grid, blk, 0, s, g, b.orders, b.first, b.count, b.drawn, b.contrib);
 }
 
 template <typename TT, int G, int V>
-void launch_apply(const GraphDev &g, int, const SnapBatch &b, hipStream_t s)
+void launch_apply(const GraphDev &g, const SnapBatch &b, hipStream_t s)
 {
     hipLaunchKernelGGL((k_snap_apply<TT, G, V>), dim3((unsigned)LH_CDIV(b.entries, 256)), dim3(256), 0, s, g, b.keys,
                        b.vals, b.entries, b.contrib, b.index);
@@ -298,15 +299,15 @@ void launch_apply(const GraphDev &g, int, const SnapBatch &b, hipStream_t s)
 
 // Lanes and elements per lane by width: four elements (16 bytes of an entry) over up to 64 lanes.
 #define LH_SNAP_WIDTH(fn, TT)                                     \
-    if (g.d <= 8) fn<TT, 2, 4>(g, orders, b, s);                  \
-    else if (g.d <= 16) fn<TT, 4, 4>(g, orders, b, s);            \
-    else if (g.d <= 32) fn<TT, 8, 4>(g, orders, b, s);            \
-    else if (g.d <= 64) fn<TT, 16, 4>(g, orders, b, s);           \
-    else if (g.d <= 128) fn<TT, 32, 4>(g, orders, b, s);          \
-    else if (g.d <= 256) fn<TT, 64, 4>(g, orders, b, s);          \
-    else fn<TT, 64, 8>(g, orders, b, s);
+    if (g.d <= 8) fn<TT, 2, 4>(g, b, s);                  \
+    else if (g.d <= 16) fn<TT, 4, 4>(g, b, s);            \
+    else if (g.d <= 32) fn<TT, 8, 4>(g, b, s);            \
+    else if (g.d <= 64) fn<TT, 16, 4>(g, b, s);           \
+    else if (g.d <= 128) fn<TT, 32, 4>(g, b, s);          \
+    else if (g.d <= 256) fn<TT, 64, 4>(g, b, s);          \
+    else fn<TT, 64, 8>(g, b, s);
 
-void contrib(const GraphDev &g, int dtype, int orders, const SnapBatch &b, hipStream_t s)
+void contrib(const GraphDev &g, int dtype, const SnapBatch &b, hipStream_t s)
 {
     if (dtype == LH_FP32) {
         LH_SNAP_WIDTH(launch_contrib, float)
@@ -315,7 +316,7 @@ void contrib(const GraphDev &g, int dtype, int orders, const SnapBatch &b, hipSt
     }
 }
 
-void apply(const GraphDev &g, int dtype, int orders, const SnapBatch &b, hipStream_t s)
+void apply(const GraphDev &g, int dtype, const SnapBatch &b, hipStream_t s)
 {
     if (dtype == LH_FP32) {
         LH_SNAP_WIDTH(launch_apply, float)
@@ -351,15 +352,15 @@ lh_status train_snapshot(lh_handle *h, unsigned long long first, unsigned long l
     for (unsigned long long b0 = first; b0 < end;) {
         unsigned long long b1 = (b0 / B + 1) * B;
         if (b1 > end) b1 = end;
-        SnapBatch b{b0, b1 - b0, b0 / B, (long long)((b1 - b0) * per), drawn, nullptr, nullptr, (float *)(h->ws + L.contrib)};
+        SnapBatch b{p.orders, b0, b1 - b0, b0 / B, (long long)((b1 - b0) * per), drawn, nullptr, nullptr, (float *)(h->ws + L.contrib)};
         hipLaunchKernelGGL(k_snap_draw, dim3((unsigned)LH_CDIV(b.count * (unsigned long long)(p.K + 1), 256)), dim3(256), 0, s, g,
                            p.orders, b.first, b.count, drawn);
         const SortBuffers sorted = radix_sort(SortArrays<1>{drawn, nullptr, nullptr, true}, b.entries, bits, two, one, hist,
                                               part, s);
         b.keys = sorted.k;
         b.vals = sorted.p0;
-        contrib(g, p.dtype, p.orders, b, s);
-        apply(g, p.dtype, p.orders, b, s);
+        contrib(g, p.dtype, b, s);
+        apply(g, p.dtype, b, s);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(h, e, "snapshot");
         b0 = b1;

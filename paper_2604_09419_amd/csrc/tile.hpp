@@ -485,31 +485,29 @@ __device__ __forceinline__ void sgd_order(const GraphDev &g, int u, const int (&
             dA[k][e] = acc;
         }
 
-    {
-        // A row that occurs more than once in this order of the sample (two slots with
-        // one row, or in first order a slot equal to the vertex row) takes the atomic
-        // path at every occurrence: each occurrence adds its own increment, computed from
-        // the rows as they were before the sample, so the row receives their sum.
-        unsigned atom = hot | (dupb << 1);
-        if constexpr (FIRST) atom |= (dupu << 1) | (dupu ? 1u : 0u);
-        // bfloat16: the sample's seed for this order; slot q's row uses seed + (q + 1) c
-        uint32_t seed = 0u;
-        if constexpr (EPU == 2) seed = lowbias32(sr);
-        constexpr uint32_t kSlot = 0x632BE59Bu;
-        // vertex row
-        write_row<TT, LPS, UPL, SH, FULL>(g, tabA, u, gl, a, dA, (atom & 1u) != 0, seed + kSlot);
-        // context rows
+    // A row that occurs more than once in this order of the sample (two slots with
+    // one row, or in first order a slot equal to the vertex row) takes the atomic
+    // path at every occurrence: each occurrence adds its own increment, computed from
+    // the rows as they were before the sample, so the row receives their sum.
+    unsigned atom = hot | (dupb << 1);
+    if constexpr (FIRST) atom |= (dupu << 1) | (dupu ? 1u : 0u);
+    // bfloat16: the sample's seed for this order; slot q's row uses seed + (q + 1) c
+    uint32_t seed = 0u;
+    if constexpr (EPU == 2) seed = lowbias32(sr);
+    constexpr uint32_t kSlot = 0x632BE59Bu;
+    // vertex row
+    write_row<TT, LPS, UPL, SH, FULL>(g, tabA, u, gl, a, dA, (atom & 1u) != 0, seed + kSlot);
+    // context rows
 #pragma unroll
-        for (int j = 0; j <= KMAX; ++j) {
-            if (FULL || j <= K) {  // (a break would keep the loop, and so b in memory)
-                float inc[UPL][EPU];
+    for (int j = 0; j <= KMAX; ++j) {
+        if (FULL || j <= K) {  // (a break would keep the loop, and so b in memory)
+            float inc[UPL][EPU];
 #pragma unroll
-                for (int k = 0; k < UPL; ++k)
+            for (int k = 0; k < UPL; ++k)
 #pragma unroll
-                    for (int e = 0; e < EPU; ++e) inc[k][e] = gj[j] * val<TT>(a[k], e) - el * val<TT>(b[j][k], e);
-                write_row<TT, LPS, UPL, SH, FULL>(g, tabB, ids[j], gl, b[j], inc, (atom & (2u << j)) != 0,
-                                                  seed + (uint32_t)(j + 2) * kSlot);
-            }
+                for (int e = 0; e < EPU; ++e) inc[k][e] = gj[j] * val<TT>(a[k], e) - el * val<TT>(b[j][k], e);
+            write_row<TT, LPS, UPL, SH, FULL>(g, tabB, ids[j], gl, b[j], inc, (atom & (2u << j)) != 0,
+                                              seed + (uint32_t)(j + 2) * kSlot);
         }
     }
 }
