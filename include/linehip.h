@@ -83,7 +83,8 @@ typedef struct {
                            probability that one sample touches r (from the degrees of the
                            last lh_build_alias), W = the launch's samples in flight
                            (unbounded when the tables fit in one XCD's L2: every touched
-                           row is hot).  Hot rows take atomic increments, the others
+                           row is hot; in the library's own binary32 shapes for d <= 64,
+                           those of a shape with four elements a lane).  Hot rows take atomic increments, the others
                            coherent (system-scope) stores.  Rows of imported alias
                            tables are hot.  <= 0: every row atomic; >= 1e30: none.       */
     double max_conflicts; /* HOGWILD: the launch keeps F samples in flight with
@@ -215,9 +216,7 @@ LH_API lh_status lh_tune(lh_handle *h, uint64_t probe, const char *cache_path);
  * one, lh_build_alias and lh_import_alias choose it from the degrees: bfloat16 handles
  * run two samples per wavefront when at most a tenth of the row touches would then fall
  * on hot rows, else one (imported tables, whose rows are all hot: one); binary32 handles
- * choose by the tables' size and the hub rows' share of the touches (where they run one
- * sample per wavefront in rows of 65 to 128 elements, launches of fewer than 2^17 samples
- * run two).  A launch runs fewer workgroups than out[2] asks for where the
+ * choose by the tables' size and the width.  A launch runs fewer workgroups than out[2] asks for where the
  * staleness cap (max_conflicts) allows no more. */
 LH_API lh_status lh_kernel_config(const lh_handle *h, int32_t out[3]);
 

@@ -575,7 +575,7 @@ lh_status build_alias(lh_handle *h, void *scratch, size_t bytes)
         return fail(h, LH_ERR_ZERO_WEIGHT, "total arc weight is zero");
     }
     h->neg_ready = h->edge_ready = true;
-    if (!h->cfg_pinned) h->cfg = auto_cfg(h);
+    choose_cfg(h);
     return LH_OK;
 }
 
@@ -626,7 +626,7 @@ lh_status import_alias(lh_handle *h, int which, const uint64_t *thr, const int32
                            (uint8_t *)(h->ws + h->lay.nheat), h->n, (uint8_t)0);
     for (int v = 0; v < 256; ++v) h->heat_count[v] = 0;
     h->heat_count[0] = (unsigned long long)h->n;
-    if (!h->cfg_pinned) h->cfg = auto_cfg(h);
+    choose_cfg(h);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "alias import");
     if (which == LH_ALIAS_EDGE)

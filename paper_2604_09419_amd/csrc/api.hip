@@ -41,6 +41,7 @@ GraphDev graph_dev(const lh_handle *h)
     g.hot_heat = -1;
     g.hot_rate = h->p.hot_rate;
     g.max_in_flight = staleness_cap(h);
+    g.narrow_flight = h->cfg_pinned ? 0.0 : h->narrow_flight;
     g.resid = small_table_window(h->l2_bytes, tables_bytes(h));
     ShadowCtx sc;
     const bool shadowed = shadow_ctx(h, &sc);
@@ -336,8 +337,8 @@ lh_status lh_train_steps(lh_handle *h, uint64_t first, uint64_t count)
             gd.pairs = pairs;
             gd.pairs_first = pf;
             gd.pool_n = pairs ? h->walk.pool : 0;
-            hipError_t le = launch_hogwild(gd, h->p.dtype, h->p.orders, launch_cfg(h, sc), sf, sf + sc,
-                                           h->num_cu, shadowed ? &shc : nullptr, h->stream);
+            hipError_t le = launch_hogwild(gd, h->p.dtype, h->p.orders, h->cfg, sf, sf + sc, h->num_cu,
+                                           shadowed ? &shc : nullptr, h->stream);
             return le == hipSuccess ? LH_OK : hip_fail(h, le, "hogwild launch");
         }
         return train_snapshot(h, sf, sc, pairs, pf);

@@ -122,6 +122,7 @@ extern "C" lh_status lh_tune(lh_handle *h, uint64_t probe, const char *cache_pat
     // masked training kernels skip), so the timing includes what the hot set costs.
     g.eta_scale = 0.0f;
     g.teams = false;  // the choice is pinned
+    g.narrow_flight = 0.0;
     const int bpc_opts[] = {1, 2, 3, 4, 8, 16};
     // Candidate shapes: the compiled (lanes, units) that cover a row with the fewest
     // 4-byte slots (wider groups would only idle lanes).

@@ -68,10 +68,11 @@ struct u64x4 {
 
 // The 128-bit product of two 64-bit words, by four 32-bit multiply-adds.  LEAN: by __umul64hi and a
 // plain product for the low word, which takes three multiplications more (a block of Philox has 341
-// instructions in place of 272) but up to 14 registers fewer.  The bfloat16 training kernels take it: their
-// samples in flight, and with them their hot rows, follow from the wavefronts that the registers allow
-// (64 lanes a sample, second order, K = 5: 74 registers and six per SIMD, or 87 and five, which turns half
-// of the atomic rows into racing ones), and their drawing is hidden.
+// instructions in place of 272) but up to 14 registers fewer.  The training kernels of bfloat16 tables and
+// of four units a lane and more take it: their samples in flight, and with them their hot rows, follow from
+// the wavefronts that the registers allow (bfloat16, 64 lanes a sample, second order, K = 5: 74 registers
+// and six per SIMD, or 87 and five, which turns half of the atomic rows into racing ones), and their
+// drawing is hidden.  The others choose their hot rows by another shape's samples in flight, or all.
 template <bool LEAN>
 __device__ __forceinline__ void mul_wide(unsigned long long a, unsigned long long b, unsigned long long &hi,
                                          unsigned long long &lo)

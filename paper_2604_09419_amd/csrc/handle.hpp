@@ -27,6 +27,8 @@ struct GraphDev {
     int hot_heat;              // rows with heat <= hot_heat take atomic increments (-1: none)
     double hot_rate;           // host side: the threshold hot_heat is derived from per launch
     double max_in_flight;      // host side: the staleness cap on samples in flight (0: none)
+    double narrow_flight;      // host side: samples in flight of a long launch with four units a lane, by
+                               // which a wider shape chooses its hot rows (0: by its own)
     double resid;              // host side: extra hot window (infinite for tables that fit in one L2)
     // bfloat16 Hogwild: binary32 shadow rows of the hot rows ([cap x d] per table) and the
     // per-node slot map (slot >= 0: the row lives in the shadow for this launch).  NULL
@@ -168,6 +170,7 @@ struct lh_handle {
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     bool timed = false;
     lh::TileCfg cfg;  // chosen Hogwild kernel configuration
+    double narrow_flight = 0.0;  // samples in flight that hot rows are chosen by at least (choose_cfg)
     bool cfg_pinned = false;  // set by lh_set_kernel_config or lh_tune: auto_cfg leaves it
     lh::WalkState walk;       // random-walk pair source, when one is built
     std::string err;
@@ -196,19 +199,20 @@ double hot_touch_share(const unsigned long long *heat_count, int hot_heat, int K
 // Samples in flight of a Hogwild launch of `count` samples in configuration c.
 double hogwild_in_flight(const GraphDev &g, int dtype, int orders, const TileCfg &c, unsigned long long count,
                          int num_cu);
-// Largest hot share at which a handle runs two samples per wavefront (binary32: rows of 65 to 128 units
-// in large tables, below).
-constexpr double kTwoPerWaveMaxHotShare = 0.1, kTwoPerWaveMaxHotShareF32 = 0.2;
-// Binary32 shapes (K = 5, second order, ns a sample on R-MAT graphs at the launch's own samples in
-// flight).  Rows of 65 to 128 units: (32, 4) up to this size of tables, which the Infinity Cache
-// still serves for the most part (300,000 nodes, 307 MB: 1.67 against 1.82), above it (64, 2),
-// whose cold rows take the streaming stores (2^20 nodes, 1.07 GB: 1.50 against 1.56), unless no more
-// than kTwoPerWaveMaxHotShareF32 of the touches fall on hot rows: then (32, 4) with its eight
-// workgroups per CU (2^20 nodes, uniform arcs and R-MAT ones mixed: share 0 1.29 against 1.60, 0.14
-// 1.40 and 1.54, 0.19 1.54 and 1.48, 0.31 1.64 and 1.50; both orders 2.61 and 3.12, 2.58 and 2.95, 2.70
-// and 2.76, 2.82 and 2.78).  Rows of
-// 33 to 64 units: (32, 2) (150,000 nodes: 1.76 against 1.78 for (64, 1) and 2.37 for (16, 4)).
-constexpr double kCachedTableBytes = 512.0 * 1048576.0;
+// Largest hot share at which a bfloat16 handle runs two samples per wavefront.
+constexpr double kTwoPerWaveMaxHotShare = 0.1;
+// Binary32 shapes.  Rows of more than 64 units: four units a lane (eight over 256 units), eight workgroups
+// per CU.  (One sample a wavefront, (64, 2) with four workgroups per CU, takes less time on large graphs with
+// hubs, 2^20 nodes, d = 128, 2 x 10^6 samples 3.05 against 3.41 ms, but by the atomics that it does not do:
+// with 4,096 samples in flight in place of 6,144 to 10,240 half of the hot rows are cold, and runs end 1.4
+// times (U 1.7) as far from runs with every row atomic.  With the same hot rows it takes 3.65 ms, and
+// without hubs 1.60 ms for 10^6 samples against 1.29.)  Rows of up to 64 units: few units a lane over many
+// lanes, (32, 2) from 33 units (150,000 nodes, K = 5, second order 1.76 ns a sample against 1.78 for
+// (64, 1) and 2.37 for (16, 4)), one unit a lane below; fewer samples are in flight then, and the hot
+// rows are those of four units a lane (narrow_flight), so that no row loses its atomics to the shape:
+// 2^20 nodes, second order, 2 x 10^6 samples, d = 16 3.67 and 1.55 ms, d = 32 3.00 and 1.66, d = 64 2.42 and
+// 2.41 (40,000 nodes, where max_conflicts sets the number for both, 2.37 and 2.19 ms for 640,000), ending
+// 0.7 to 1.0 times as far from runs with every row atomic.
 // Tables that fit in one L2 have every row updated atomically: no update is lost, and what a run
 // ends with depends on the order in which samples are taken.  With four units a lane (few lanes a
 // sample, many samples a wavefront) a binary32 launch spends its rounds issuing accesses; with one
@@ -257,13 +261,8 @@ inline double staleness_cap(const lh_handle *h)
 // in large tables, but they also enlarge the hot set, whose atomics cost more than that
 // gain where hub rows take a large share of the touches.  Binary32: as above.
 TileCfg auto_cfg(const lh_handle *h);
-// The configuration of a launch of `count` samples: the handle's, but where auto_cfg chose (64, 2) for
-// binary32 a launch of fewer than kShortLaunch samples takes (32, 4).  With fewer tiles than wavefronts a
-// sample a wavefront leaves half as many in flight (2^20 nodes, d = 128, hub rows: 40,000 samples 112
-// against 71 us, 64,000 127 and 94, 130,000 215 and 209; both orders 158 and 129, 202 and 193, 385 and
-// 405).
-constexpr unsigned long long kShortLaunch = 1ull << 17;
-TileCfg launch_cfg(const lh_handle *h, unsigned long long count);
+// Take it, and the samples in flight of four units a lane, unless a configuration is pinned.
+void choose_cfg(lh_handle *h);
 bool cfg_supported(int dtype, int d, const TileCfg &c);
 hipError_t launch_hogwild(const GraphDev &g, int dtype, int orders, const TileCfg &c,
                           unsigned long long first, unsigned long long end, int num_cu,

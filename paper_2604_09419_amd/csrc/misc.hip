@@ -103,17 +103,18 @@ TileCfg natural_cfg(int dtype, int d)
     return c;
 }
 
-// The Hogwild configuration before any tuning or degrees: one sample per wavefront, one 4-byte
-// unit per lane over up to 64 lanes (wider rows: more units per lane; rows of at most 32 units:
-// as many lanes as units, at least 16).  Spreading a row over lanes rather than over a lane's
-// registers makes each access cover whole lines, and for a given number of samples in flight it
-// spreads them over more wavefronts: with four units a lane over few lanes, binary32 with K = 5
-// and second order took 3.1 against 1.5 ns a sample at d = 16 and 250,000 nodes.  Four workgroups
-// per CU for binary32: eight double the hot set (2^20 nodes, d = 128: 1.81 against 1.51 ns);
-// bfloat16's sixteen are what its registers leave of them.
+// The Hogwild configuration before any tuning or degrees.  Binary32 rows of more than 64 units: four
+// units a lane.  Else one sample per wavefront, one 4-byte unit per lane over up to 64 lanes (wider
+// bfloat16 rows: more units per lane; rows of at most 32 units: as many lanes as units, at least 16).
+// Spreading a row over lanes rather than over a lane's registers makes each access cover whole lines, and
+// for a given number of samples in flight it spreads them over more wavefronts: with four units a lane
+// over few lanes, binary32 with K = 5 and second order took 3.1 against 1.5 ns a sample at d = 16 and
+// 250,000 nodes.  Four workgroups per CU for these binary32 rows; bfloat16's sixteen are what its
+// registers leave of them.
 TileCfg default_cfg(int dtype, int d)
 {
     const int nu = units_per_row(dtype, d);
+    if (dtype == LH_FP32 && nu > 64) return natural_cfg(dtype, d);
     TileCfg c;
     c.blocks_per_cu = dtype == LH_FP32 ? 4 : 16;
     if (nu <= 64) {
@@ -150,21 +151,12 @@ double hogwild_in_flight(const GraphDev &g, int dtype, int orders, const TileCfg
     return hogwild_in_flight_t<uint16_t, 3>(g, c, count, num_cu);
 }
 
-// Share of the row touches that fall on hot rows in a launch of configuration c (1: no such kernel).
-static double hot_share(const lh_handle *h, const TileCfg &c)
-{
-    const GraphDev g = graph_dev(h);
-    const double F = hogwild_in_flight(g, h->p.dtype, h->p.orders, c, h->p.total_samples, h->num_cu);
-    return F > 0.0 ? hot_touch_share(h->heat_count, hot_heat_for(F + g.resid, g.hot_rate), h->p.K) : 1.0;
-}
-
-// Binary32 shapes, by the tables' size and the hub rows' share of the touches (see handle.hpp).
-static TileCfg auto_cfg_f32(const lh_handle *h, const TileCfg &wide)
+// Binary32 shapes, by the tables' size and the width (see handle.hpp).
+static TileCfg auto_cfg_f32(const lh_handle *h)
 {
     const int nu = h->p.d;
-    const double bytes = tables_bytes(h);
-    TileCfg c = wide;
-    if (small_table_window(h->l2_bytes, bytes) > 0.0) {
+    TileCfg c = default_cfg(h->p.dtype, h->p.d);
+    if (small_table_window(h->l2_bytes, tables_bytes(h)) > 0.0) {
         c = natural_cfg(h->p.dtype, h->p.d);  // four units a lane, or teams of narrower lanes
         if (nu <= 16) {
             c.lps = 16;
@@ -173,9 +165,6 @@ static TileCfg auto_cfg_f32(const lh_handle *h, const TileCfg &wide)
             c.lps *= 2;
             c.upl = 2;
         }
-    } else if (nu > 64 && nu <= 128) {  // (64, 2) or (32, 4)
-        const TileCfg two = natural_cfg(h->p.dtype, h->p.d);
-        if (bytes <= kCachedTableBytes || hot_share(h, two) <= kTwoPerWaveMaxHotShareF32) c = two;
     } else if (nu > 32 && nu <= 64) {
         c.lps = 32;
         c.upl = 2;
@@ -188,19 +177,26 @@ TileCfg auto_cfg(const lh_handle *h)
 {
     const TileCfg one = default_cfg(h->p.dtype, h->p.d);
     if (h->p.mode != LH_HOGWILD) return one;
-    if (h->p.dtype == LH_FP32) return auto_cfg_f32(h, one);
+    if (h->p.dtype == LH_FP32) return auto_cfg_f32(h);
     TileCfg two = one;
     two.lps = one.lps / 2;
     two.upl = one.upl * 2;
     if (!cfg_supported(h->p.dtype, h->p.d, two)) return one;
-    return hot_share(h, two) <= kTwoPerWaveMaxHotShare ? two : one;
+    const GraphDev g = graph_dev(h);
+    const double F = hogwild_in_flight(g, h->p.dtype, h->p.orders, two, h->p.total_samples, h->num_cu);
+    if (!(F > 0.0)) return one;
+    const int hot = hot_heat_for(F + g.resid, g.hot_rate);
+    return hot_touch_share(h->heat_count, hot, h->p.K) <= kTwoPerWaveMaxHotShare ? two : one;
 }
 
-TileCfg launch_cfg(const lh_handle *h, unsigned long long count)
+void choose_cfg(lh_handle *h)
 {
-    const bool one = !h->cfg_pinned && h->p.dtype == LH_FP32 && h->cfg.lps == 64 && h->cfg.upl == 2 &&
-                     tables_bytes(h) > kCachedTableBytes;
-    return one && count < kShortLaunch ? natural_cfg(h->p.dtype, h->p.d) : h->cfg;
+    if (h->cfg_pinned) return;
+    h->cfg = auto_cfg(h);
+    h->narrow_flight = 0.0;
+    if (h->p.mode == LH_HOGWILD && h->p.dtype == LH_FP32 && h->cfg.lps > four_unit_lanes(h->p.d))
+        h->narrow_flight = hogwild_in_flight(graph_dev(h), h->p.dtype, h->p.orders, natural_cfg(h->p.dtype, h->p.d),
+                                             1ull << 40, h->num_cu);
 }
 
 bool cfg_supported(int dtype, int d, const TileCfg &c)

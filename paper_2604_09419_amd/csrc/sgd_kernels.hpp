@@ -192,6 +192,15 @@ inline HogwildPlan plan_launch(KernelT kern, int lps, int team, const GraphDev &
     return p;
 }
 
+// The samples in flight that hot rows are chosen by: the launch's, or those that four units a lane would
+// have (a tile of 64 samples a wavefront), if more.
+inline double hot_window(const GraphDev &g, const HogwildPlan &p, unsigned long long count)
+{
+    if (!(g.narrow_flight > p.in_flight)) return p.in_flight;
+    const double tiles = (double)(((count - 1) >> 8) + 1) * 4.0;  // (whole workgroups)
+    return std::max(p.in_flight, std::min(g.narrow_flight, tiles * (64 / four_unit_lanes(g.nunits))));
+}
+
 // One Hogwild launch with the heat threshold for its concurrency.  With a shadow context
 // (bfloat16 tables) the hot rows move into the binary32 shadow for the launch and back
 // afterwards; without one no row is read from a shadow.
@@ -201,7 +210,7 @@ hipError_t launch_one(KernelT kern, int lps, int team, const GraphDev &g, const 
 {
     const HogwildPlan p = plan_launch(kern, lps, team, g, c, end - first, num_cu);
     GraphDev gl = g;
-    gl.hot_heat = hot_heat_for(p.in_flight + g.resid, g.hot_rate);
+    gl.hot_heat = hot_heat_for(hot_window(g, p, end - first) + g.resid, g.hot_rate);
     gl.tile_shift = p.tile_shift;
     gl.streams = p.streams;
     gl.q_shift = p.q_shift;

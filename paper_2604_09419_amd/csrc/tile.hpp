@@ -562,7 +562,7 @@ __device__ __forceinline__ void sgd_tile(const GraphDev &g, const TileAt &at, in
             // One Philox block at a time, its record load issued at once, so the loads of
             // all 1 + K slots are in flight together while the blocks are not interleaved
             // (which would hold 1 + K blocks of state in registers).
-            constexpr bool LEAN = sizeof(TT) == 2;
+            constexpr bool LEAN = sizeof(TT) == 2 || UPL >= 4;  // (see mul_wide)
             const SlotDraw de = draw_slot<LEAN>(g, s, 0, slot0_columns(g));
             uint4 r0, r1;
             load_pair_rec<sizeof(TT) == 2>(g, s, de.col, de.x1, r0, r1);

@@ -1,12 +1,12 @@
-"""Registers of the bfloat16 Hogwild kernels, from the metadata of the code objects in the built library.
+"""Registers of the Hogwild kernels, from the metadata of the code objects in the built library.
 
-Both orders with several samples a wavefront spill nothing: a register that the sampling loop spills costs a
-scratch load there, and its wait also waits for the acknowledgements of the stores before it.
+Both orders of bfloat16 with several samples a wavefront spill nothing: a register that the sampling loop
+spills costs a scratch load there, and its wait also waits for the acknowledgements of the stores before it.
 
-One order with a wavefront a sample stays within 80 registers, six wavefronts per SIMD (512 / 80).  The hot
-set follows the samples in flight, 256 x 4 x 6 here, and heats are whole powers of two: rows that a sample
-touches with probability 2^-13 to 2^-14 are hot at the default threshold with six (6144 / 0.75 = 2^13) and
-cold with five."""
+One order with a wavefront a sample (bfloat16 up to two units a lane, binary32 with four) stays within 80
+registers, six wavefronts per SIMD (512 / 80).  The hot set follows the samples in flight, 256 x 4 x 6 here,
+and heats are whole powers of two: rows that a sample touches with probability 2^-13 to 2^-14 are hot at the
+default threshold with six (6144 / 0.75 = 2^13) and cold with five."""
 import re
 import struct
 
@@ -60,9 +60,10 @@ def test_both_orders_bfloat16_kernels_spill_nothing(kernels, lanes, units):
     assert [k[".vgpr_spill_count"] for k in found] == [0, 0]
 
 
-@pytest.mark.parametrize("lanes,units,order", [(64, 1, 1), (64, 1, 2), (64, 2, 1)])
-def test_one_order_bfloat16_kernels_fit_six_wavefronts(kernels, lanes, units, order):
+@pytest.mark.parametrize("table,lanes,units,order", [("t", 64, 1, 1), ("t", 64, 1, 2), ("t", 64, 2, 1), ("f", 64, 4, 1),
+                                                     ("f", 64, 4, 2)])
+def test_one_order_kernels_fit_six_wavefronts(kernels, table, lanes, units, order):
     found = [k for name, k in kernels.items()
-             if re.search(rf"k_hogwildItLi{lanes}ELi{units}ELi5ELi{order}ELb0ELb1E", name)]
+             if re.search(rf"k_hogwildI{table}Li{lanes}ELi{units}ELi5ELi{order}ELb0ELb1E", name)]
     assert len(found) == 1
     assert found[0][".vgpr_count"] <= 80
