@@ -17,11 +17,14 @@ namespace lh {
 // waves for one unit a lane and 3 for more, nothing is spilled; graphs without hubs, 5 waves and so:
 // 40,000 nodes, 640,000 samples, d = 32 1.25 and 1.09 ms, d = 128 2.73 and 1.27, d = 256 7.0 and 1.93;
 // 2^20 nodes, 10^6 samples, d = 128 2.34 and 1.34 (4 waves and 3 spilled registers 1.32).
-template <typename TT, int LPS, int UPL, int ORD>
+// First order with a wavefront a sample and up to five negatives: 80 registers suffice for 6, and the hot
+// set stays.  With up to eight 6 would spill (2 registers) and enlarge the hot set, which follows the
+// samples in flight: rows of 2^-13 to 2^-14 a sample are hot with 6,144 of them, not with 5,120.
+template <typename TT, int LPS, int UPL, int KMAX, int ORD>
 constexpr int hogwild_min_waves()
 {
     if (sizeof(TT) == 4) return 3;
-    if (ORD == 1 && LPS == 64 && UPL <= 2) return 6;  // (80 registers suffice, and the hot set stays)
+    if (ORD == 1 && LPS == 64 && UPL <= 2 && KMAX <= 5) return 6;
     return ORD == 3 && LPS < 64 ? (UPL > 1 ? 3 : 4) : 5;
 }
 
@@ -36,8 +39,9 @@ constexpr int hogwild_min_waves()
 // FULL: the tile shape covers a row exactly (lanes x units == the row's units) and K == KMAX,
 // so row accesses need no bounds mask or slot test.
 template <typename TT, int LPS, int UPL, int KMAX, int ORD, bool SH, bool FULL = false>
-__global__ void __launch_bounds__(256, (hogwild_min_waves<TT, LPS, UPL, ORD>())) k_hogwild(GraphDev g, unsigned long long first,
-                                                                                     unsigned long long end)
+__global__ void __launch_bounds__(256, (hogwild_min_waves<TT, LPS, UPL, KMAX, ORD>())) k_hogwild(GraphDev g,
+                                                                                           unsigned long long first,
+                                                                                           unsigned long long end)
 {
     const unsigned lane = threadIdx.x & 63u;
     __shared__ unsigned long long next;
