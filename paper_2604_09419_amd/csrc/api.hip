@@ -43,6 +43,8 @@ GraphDev graph_dev(const lh_handle *h)
     g.max_in_flight = staleness_cap(h);
     g.narrow_flight = h->cfg_pinned ? 0.0 : h->narrow_flight;
     g.resid = small_table_window(h->l2_bytes, tables_bytes(h));
+    g.heat_count = h->p.dtype == LH_BF16 && h->p.K > 5 ? h->heat_count : nullptr;
+    g.paced = false;
     ShadowCtx sc;
     const bool shadowed = shadow_ctx(h, &sc);
     for (int t = 0; t < 3; ++t) g.shadow[t] = shadowed ? sc.shadow[t] : nullptr;

@@ -30,6 +30,10 @@ struct GraphDev {
     double narrow_flight;      // host side: samples in flight of a long launch with four units a lane, by
                                // which a wider shape chooses its hot rows (0: by its own)
     double resid;              // host side: extra hot window (infinite for tables that fit in one L2)
+    // bfloat16 with more than five negatives.  Host side: nodes per heat value (else NULL); the launch's
+    // choice: a sample's context rows are loaded one at a time (paced_loads).
+    const unsigned long long *heat_count;
+    bool paced;
     // bfloat16 Hogwild: binary32 shadow rows of the hot rows ([cap x d] per table) and the
     // per-node slot map (slot >= 0: the row lives in the shadow for this launch).  NULL
     // for binary32 tables and SNAPSHOT.

@@ -205,16 +205,34 @@ inline double hot_window(const GraphDev &g, const HogwildPlan &p, unsigned long 
     return std::max(p.in_flight, std::min(g.narrow_flight, tiles * (64 / four_unit_lanes(g.nunits))));
 }
 
+// Samples in flight on the hottest row from which context rows are loaded one at a time.
+constexpr double kPacedQueue = 128.0;
+
+// Whether a bfloat16 launch with more than five negatives and one unit a lane waits for each context row
+// before it loads the next.  With this many samples in flight wanting the graph's hottest row (by its heat,
+// a whole power of two), memory is busy with the queue for it, and loads that are in flight together only
+// lengthen it; otherwise rows in flight together take less time.  400,000 nodes, d = 32, both orders, six
+// negatives, 10^6 samples, together and one at a time: 177 samples on the hottest row 1.91 and 1.69 ms, 93
+// 1.02 and 1.21.  (Five negatives or fewer: rows together.)
+template <typename TT>
+inline bool paced_loads(const GraphDev &g, const TileCfg &c, const HogwildPlan &p)
+{
+    if (sizeof(TT) != 2 || !g.heat_count || c.upl != 1) return false;
+    int v = 0;
+    while (v < 255 && !g.heat_count[v]) ++v;
+    return p.in_flight * std::exp2(-(v + 0.5)) > kPacedQueue;
+}
 // One Hogwild launch with the heat threshold for its concurrency.  With a shadow context
 // (bfloat16 tables) the hot rows move into the binary32 shadow for the launch and back
 // afterwards; without one no row is read from a shadow.
-template <typename KernelT>
+template <typename TT, typename KernelT>
 hipError_t launch_one(KernelT kern, int lps, int team, const GraphDev &g, const TileCfg &c, unsigned long long first,
                       unsigned long long end, int num_cu, const ShadowCtx *sc, hipStream_t s)
 {
     const HogwildPlan p = plan_launch(kern, lps, team, g, c, end - first, num_cu);
     GraphDev gl = g;
     gl.hot_heat = hot_heat_for(hot_window(g, p, end - first) + g.resid, g.hot_rate);
+    gl.paced = paced_loads<TT>(g, c, p);
     gl.tile_shift = p.tile_shift;
     gl.streams = p.streams;
     gl.q_shift = p.q_shift;
@@ -279,9 +297,9 @@ hipError_t launch_hogwild_sh(const GraphDev &g, const TileCfg &c, unsigned long 
 #define LH_LAUNCH_H(L, C)                                                                        \
     if (c.lps == L && c.upl == C) {                                                              \
         if (!SH && g.K == 5 && L * C == g.nunits)                                                \
-            return launch_one(k_hogwild<TT, L, C, 5, ORD, false, true>, L, team, g, c, first, end, num_cu, sc, s); \
-        if (k5) return launch_one(k_hogwild<TT, L, C, 5, ORD, SH>, L, team, g, c, first, end, num_cu, sc, s); \
-        return launch_one(k_hogwild<TT, L, C, 8, ORD, SH>, L, team, g, c, first, end, num_cu, sc, s);        \
+            return launch_one<TT>(k_hogwild<TT, L, C, 5, ORD, false, true>, L, team, g, c, first, end, num_cu, sc, s); \
+        if (k5) return launch_one<TT>(k_hogwild<TT, L, C, 5, ORD, SH>, L, team, g, c, first, end, num_cu, sc, s); \
+        return launch_one<TT>(k_hogwild<TT, L, C, 8, ORD, SH>, L, team, g, c, first, end, num_cu, sc, s);        \
     }
     LH_CFG_LIST(LH_LAUNCH_H)
 #undef LH_LAUNCH_H

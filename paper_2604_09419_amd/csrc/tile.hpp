@@ -312,6 +312,9 @@ __device__ __forceinline__ void load_rows(Rows<TT, UPL, KMAX> &r, const GraphDev
 #pragma unroll
     for (int j = 0; j <= KMAX; ++j) {
         if (FULL || j <= K) {
+            // (vmcnt 0, the other counters left alone: paced_loads says when)
+            if constexpr (sizeof(TT) == 2 && KMAX > 5 && UPL == 1)
+                if (g.paced) __builtin_amdgcn_s_waitcnt(0x0F70);
             load_row_raw<TT, LPS, UPL, SH, FULL>(g, tB, ids[j], gl, r.b[j], bh[j]);
         } else {
 #pragma unroll
