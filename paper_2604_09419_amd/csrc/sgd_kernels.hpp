@@ -12,11 +12,15 @@ namespace lh {
 // Register budget of the one-graph kernel: at least 3 (binary32) or 5 (bfloat16) waves per
 // SIMD.  The bfloat16 kernel is latency bound: 5 waves (96 registers, no spills) measured
 // 2 % faster than 4 on both hub-heavy and large uniform tables, and 6 (with spills) slower.
-// Both orders with several samples a wavefront do not fit 96 registers: what is spilled is read back in
+// Both orders with several samples a wavefront, and one order with four units a lane or more, do not fit 96
+// registers (the hot set is the same with 5 waves and with 3, 10,240 and 6,144 samples in flight or a power
+// of two times that): what is spilled is read back in
 // every round, and the wait for that also waits for the stores before it to be acknowledged.  With 4
-// waves for one unit a lane and 3 for more, nothing is spilled; graphs without hubs, 5 waves and so:
+// waves for one unit a lane and 3 for more, nothing is spilled up to four units; graphs without hubs, 5 waves and so:
 // 40,000 nodes, 640,000 samples, d = 32 1.25 and 1.09 ms, d = 128 2.73 and 1.27, d = 256 7.0 and 1.93;
-// 2^20 nodes, 10^6 samples, d = 128 2.34 and 1.34 (4 waves and 3 spilled registers 1.32).
+// 2^20 nodes, 10^6 samples, d = 128 2.34 and 1.34 (4 waves and 3 spilled registers 1.32); one order, four
+// or eight units a lane, 300,000 nodes, 500,000 samples, d = 256 1.4 times as fast, d = 512 2.3 times.
+// Fewer than 16 lanes keep 5: graphs with hubs, d = 64 on (8, 4), 3 waves take 1.12-1.17 of that time.
 // First order with a wavefront a sample and up to five negatives: 80 registers suffice for 6, and the hot
 // set stays.  With up to eight 6 would spill (2 registers) and enlarge the hot set, which follows the
 // samples in flight: rows of 2^-13 to 2^-14 a sample are hot with 6,144 of them, not with 5,120.
@@ -25,7 +29,7 @@ constexpr int hogwild_min_waves()
 {
     if (sizeof(TT) == 4) return 3;
     if (ORD == 1 && LPS == 64 && UPL <= 2 && KMAX <= 5) return 6;
-    return ORD == 3 && LPS < 64 ? (UPL > 1 ? 3 : 4) : 5;
+    return LPS < 64 && (ORD == 3 || (LPS >= 16 && UPL >= 4)) ? (UPL > 1 ? 3 : 4) : 5;
 }
 
 // SH: bfloat16 tables whose hot rows live in a binary32 shadow for the launch.  Each

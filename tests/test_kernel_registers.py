@@ -76,3 +76,11 @@ def test_one_order_kernels_for_more_negatives_keep_five_wavefronts(kernels, unit
     assert len(found) == 1
     assert found[0][".vgpr_spill_count"] == 0
     assert 80 < found[0][".vgpr_count"] <= 96
+
+
+@pytest.mark.parametrize("lanes", [16, 32])
+@pytest.mark.parametrize("order", [1, 2])
+def test_narrow_four_unit_kernels_spill_nothing(kernels, lanes, order):
+    found = [k for name, k in kernels.items() if re.search(rf"k_hogwildItLi{lanes}ELi4ELi5ELi{order}ELb0ELb[01]E", name)]
+    assert len(found) == 2
+    assert [k[".vgpr_spill_count"] for k in found] == [0, 0]
