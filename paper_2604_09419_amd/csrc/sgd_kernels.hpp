@@ -226,6 +226,7 @@ inline bool paced_loads(const GraphDev &g, const TileCfg &c, const HogwildPlan &
     while (v < 255 && !g.heat_count[v]) ++v;
     return p.in_flight * std::exp2(-(v + 0.5)) > kPacedQueue;
 }
+
 // One Hogwild launch with the heat threshold for its concurrency.  With a shadow context
 // (bfloat16 tables) the hot rows move into the binary32 shadow for the launch and back
 // afterwards; without one no row is read from a shadow.
